@@ -243,7 +243,8 @@ const char *lstm_last_error_detail(void);
  * fwd variant, bwd workgroups, bwd cells per workgroup, bwd batch rows per
  * tile, bwd variant}; a workgroup count of 0 means no tiling fits.  Variant
  * 1000 marks the XCD-local kernels (bf16, plain LSTM, H in {256, 512, 1024}:
- * each XCD owns ceil(B/8) batch rows, each workgroup H/32 cells). */
+ * each XCD owns ceil(B/8) batch rows, each workgroup H/32 cells), 1001 the
+ * same kernels on any other H up to 1024 (8, 16 or 32 cells per workgroup). */
 lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8);
 
 /* Elementwise out[i] = a[i] + b[i] for i < n, in fp32 arithmetic, rounded to

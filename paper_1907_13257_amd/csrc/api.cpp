@@ -98,6 +98,16 @@ bool use_stepwise(const lstm_handle *h, bool persistent_ok)
     return h->d.Hp > 0 && h->d.H >= 2048;
 }
 
+// Whether the layer runs on the XCD-local kernels: every shape they take,
+// except that LSTM355_RECURRENCE=stepwise (testing) still selects the
+// stepwise sequence for the widths that are padded.
+bool use_xcd(const lstm_handle *h, const RecShape &sh)
+{
+    if (!xcd_path_ok(h->dt, sh, h->num_cus)) return false;
+    const char *env = xcd_full_width(sh) ? nullptr : std::getenv("LSTM355_RECURRENCE");
+    return !(env && std::strcmp(env, "stepwise") == 0);
+}
+
 #define TRY_HIP(what, expr)                                  \
     do {                                                     \
         hipError_t e_ = (expr);                              \
@@ -241,7 +251,7 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     fb.ms = d.Hp ? rv + h->r_ms : nullptr;
     fb.y = y; fb.hT = hT; fb.cT = cT;
     fb.sync = reinterpret_cast<unsigned *>(wv + h->w_sync);
-    const bool xcd = xcd_path_ok(h->dt, sh, h->num_cus);
+    const bool xcd = use_xcd(h, sh);
     if (xcd && h->r_act16) fb.act16 = rv + h->r_act16;
 
     GemmDesc g{};
@@ -252,7 +262,7 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     g.C = gates; g.ldc = h->G4;
     g.bias = b; g.beta = 0;
     if (xcd) g.side = xcd_prep_forward(sh, fb);   // the recurrence's exchange rows and flags
-    if (xcd && full_ws) {
+    if (xcd && full_ws && xcd_full_width(sh)) {
         // the XCD-local forward takes the input projection in fp16, half the
         // bytes of the product's output and of the recurrence's reads, in the
         // workspace's dz rows (the backward's, unused by the forward)
@@ -343,7 +353,7 @@ extern "C" lstm_status_t lstm_forward_noalloc(lstm_handle_t h, const void *x, co
         // sequence (wide LSTMP layers) needs split-K partials as well
         const lstm_desc_t &d = h->d;
         RecShape sh{d.T, d.B, d.I, d.H, d.Hp, d.reverse, h->ldy};
-        const bool stepwise = !xcd_path_ok(h->dt, sh, h->num_cus) && use_stepwise(h, h->fwd_ok);
+        const bool stepwise = !use_xcd(h, sh) && use_stepwise(h, h->fwd_ok);
         const size_t need = stepwise ? h->w_split + h->split_floats * 4 : h->w_sync + SYNC_BYTES;
         if (need > NOALLOC_SCRATCH_BYTES) {
             std::snprintf(g_detail, sizeof(g_detail),
@@ -656,7 +666,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
         float *split_ws = reinterpret_cast<float *>(wv + h->w_split);
 
         RecShape sh{T, B, I, H, Hp, d.reverse, h->ldy};
-        const bool xcd = xcd_path_ok(h->dt, sh, h->num_cus);
+        const bool xcd = use_xcd(h, sh);
         const bool stepwise = !xcd && use_stepwise(h, h->bwd_ok);
 
         BwdBufs bb{};
@@ -826,7 +836,7 @@ extern "C" lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8)
     lstm_status_t st = ensure_plan(h);
     if (st != LSTM_OK) return st;
     RecShape sh{h->d.T, h->d.B, h->d.I, h->d.H, h->d.Hp, h->d.reverse, h->ldy};
-    const bool xcd = xcd_path_ok(h->dt, sh, h->num_cus);
+    const bool xcd = use_xcd(h, sh);
     if (!xcd && use_stepwise(h, h->fwd_ok && h->bwd_ok)) {
         // stepwise sequence: GEMM launches per step, no persistent grid
         const int v[8] = {0, 0, h->d.B, STEPWISE_VARIANT, 0, 0, h->d.B, STEPWISE_VARIANT};
@@ -834,9 +844,11 @@ extern "C" lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8)
         return LSTM_OK;
     }
     if (xcd) {
-        // XCD-local kernels: 256 workgroups, H/32 cells each, ceil(B/8) rows per XCD
+        // XCD-local kernels: 256 workgroups, 8, 16 or 32 cells each, ceil(B/8) rows per XCD
         const int rx = (h->d.B + 7) / 8;
-        const int v[8] = {256, h->d.H / 32, rx, XCD_VARIANT, 256, h->d.H / 32, rx, XCD_VARIANT};
+        const int hn = h->d.H <= 256 ? 8 : (h->d.H <= 512 ? 16 : 32);
+        const int var = xcd_full_width(sh) ? XCD_VARIANT : XCD_PAD_VARIANT;
+        const int v[8] = {256, hn, rx, var, 256, hn, rx, var};
         for (int i = 0; i < 8; ++i) out8[i] = v[i];
         return LSTM_OK;
     }

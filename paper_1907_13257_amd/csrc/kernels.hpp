@@ -231,10 +231,15 @@ constexpr int XCD_WORDS = 257;     // words cleared before an XCD-local launch
 // 2 = an XCD-local launch did not give every (XCD, slot) role exactly one workgroup.
 constexpr unsigned TRIP_WATCHDOG = 1u, TRIP_PLACEMENT = 2u;
 
-// XCD-local recurrences (recurrent_xcd.hip): bf16, plain LSTM, H in {256,
-// 512, 1024}, exactly 256 CUs.
+// XCD-local recurrences (recurrent_xcd.hip): bf16, plain LSTM, H a multiple
+// of 8 up to 1024, exactly 256 CUs.
 bool xcd_path_ok(DType t, const RecShape &sh, int num_cus);
-constexpr int XCD_VARIANT = 1000;   // variant reported by lstm_describe_tiling for these kernels
+// H in {256, 512, 1024}: every workgroup of an XCD owns its full share of
+// cells.  Only these layers keep fp16 intermediates.
+bool xcd_full_width(const RecShape &sh);
+// variants reported by lstm_describe_tiling for these kernels: full widths,
+// and the other widths padded with zero weights to the next full one
+constexpr int XCD_VARIANT = 1000, XCD_PAD_VARIANT = 1001;
 void xcd_path_disable();
 hipError_t xcd_tripped_read_and_clear(unsigned *tripped);   // like watchdog_read_and_clear
 unsigned long long watchdog_ticks();

@@ -1,5 +1,5 @@
 // recurrent_xcd.hip -- persistent forward / BPTT recurrences whose per-step
-// exchange stays inside one XCD (bf16, plain LSTM, H in {256, 512, 1024}).
+// exchange stays inside one XCD (bf16, plain LSTM, H up to 1024).
 //
 // The MI355X has 8 XCDs of 32 CUs, each XCD with its own L2; a 256-workgroup
 // launch puts 32 workgroups on each XCD, and a workgroup takes the XCD it
@@ -92,10 +92,13 @@ __device__ __forceinline__ int stage_swz(int r)
 // the 1 KiB instructions are issued starting at `rot` (mod their count), so
 // that the workgroups of an XCD, which all copy the same rows, start on
 // different lines of L2 (measured: 2% faster for the forward's four
-// instructions per wave, slower for the backward's sixteen).
-template <int RB, bool COHERENT = false, bool ROT = false>
+// instructions per wave, slower for the backward's sixteen).  PAD: bytes of a
+// row at or past kend read as zero (an offset past the descriptor's end).
+constexpr unsigned OOB_OFFSET = 0x80000000u;
+
+template <int RB, bool COHERENT = false, bool ROT = false, bool PAD = false>
 __device__ __forceinline__ void stage_rows(u32x4 rs, long r0, long ld, int kbyte, unsigned tile, int lane,
-                                           unsigned qmask = ~0u, int rot = 0)
+                                           unsigned qmask = ~0u, int rot = 0, int kend = 0)
 {
     static_assert(RB % 64 == 0 && (16 * RB) % 1024 == 0, "whole 1 KiB instructions");
     constexpr int NQ = 16 * RB / 1024;
@@ -107,7 +110,8 @@ __device__ __forceinline__ void stage_rows(u32x4 rs, long r0, long ld, int kbyte
         const int o = q * 1024 + lane * 16;
         const int r = o / RB, p = (o % RB) >> 4;
         const int c = p ^ stage_swz<RB>(r);
-        const unsigned voff = (unsigned)((r0 + r) * ld * 2 + kbyte + c * 16);
+        unsigned voff = (unsigned)((r0 + r) * ld * 2 + kbyte + c * 16);
+        if (PAD && kbyte + c * 16 >= kend) voff = OOB_OFFSET;
         if (COHERENT)
             dma16_sc1(rs, __builtin_amdgcn_readfirstlane(tile + q * 1024), voff);
         else
@@ -156,11 +160,12 @@ __device__ __forceinline__ bool saw_not_ready(u16x2 m) { return m.x == NOT_READY
 // and multiplies it while checking for NOT_READY; an attempt that saw one is
 // discarded and repeated.  Returns false if another workgroup aborted or the
 // wall-clock watchdog expired (then the abort word is raised).
-template <int RB, int KCW, int NBX, bool WT = false>
+template <int RB, int KCW, int NBX, bool WT = false, bool PAD = false>
 __device__ __forceinline__ bool stage_mma_when_ready(u32x4 rs, long r0, long ld, int kbyte, unsigned tile,
                                                      const char *tilep, int lane, int valid,
                                                      const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX],
-                                                     unsigned *flags, unsigned long long timeout, int rot)
+                                                     unsigned *flags, unsigned long long timeout, int rot,
+                                                     int kend = 0)
 {
     constexpr int RPI = 1024 / RB > 0 ? 1024 / RB : 1;   // rows per 1 KiB instruction (RB <= 1024)
     static_assert(RB <= 1024, "one row per instruction at most");
@@ -174,7 +179,7 @@ __device__ __forceinline__ bool stage_mma_when_ready(u32x4 rs, long r0, long ld,
     for (int q = 0; q < 16 / RPI; ++q)
         if (q * RPI < valid) qmask |= 1u << q;
     while (true) {
-        stage_rows<RB, true, WT>(rs, r0, ld, kbyte, tile, lane, qmask, rot);
+        stage_rows<RB, true, WT, PAD>(rs, r0, ld, kbyte, tile, lane, qmask, rot, kend);
         const unsigned ab = __builtin_amdgcn_raw_buffer_load_b32(rfl, XCD_ABORT * 4, 0, 16);
         wait_own_loads();
 #pragma unroll
@@ -223,8 +228,6 @@ __device__ __forceinline__ bool stage_mma_when_ready(u32x4 rs, long r0, long ld,
 // which puts the 16 rows that one fragment read touches in distinct banks.
 // Rows at or past `valid` are not copied (an offset past the descriptor's end
 // loads zeros).
-constexpr unsigned OOB_OFFSET = 0x80000000u;
-
 __device__ __forceinline__ unsigned pair_voff(long r0, long ld, int kbyte, int lane, int h, int valid)
 {
     const int r = 8 * h + (lane >> 3), piece = (lane & 7) ^ ((r >> 1) & 7);
@@ -262,24 +265,29 @@ __device__ __forceinline__ void wait_loads_upto(int n)
 // with every later pair (they were copied at the same time, so they are
 // likely stale too), until it is complete.  Chunks are multiplied in order,
 // so the sums are those of the unpipelined form, bit for bit.
-template <int KCW, int NBX, int G>
+template <int KCW, int NBX, int G, bool PAD = false>
 __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int kbyte, unsigned tile,
                                                const char *tilep, int lane, int valid,
                                                const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX], unsigned *flags,
-                                               unsigned long long timeout)
+                                               unsigned long long timeout, int kend = 0)
 {
     static_assert(KCW >= 2 && KCW <= 16 && KCW % 2 == 0, "whole chunk pairs, at most 16 instructions in flight");
     static_assert(G % 2 == 0 && KCW % G == 0, "whole pairs per group, whole groups");
     const unsigned v0 = pair_voff(r0, ld, kbyte, lane, 0, valid);
     const unsigned v1 = pair_voff(r0, ld, kbyte, lane, 1, valid);
     const bool row_in = (lane & 15) < valid;
+    // PAD: first byte of this lane's piece of pair 0 within the row, per instruction
+    const int kb0 = kbyte + ((lane & 7) ^ ((lane >> 4) & 7)) * 16;
+    const int kb1 = kbyte + ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) * 16;
     auto issue_from = [&](int p0) {
 #pragma unroll
         for (int p = 0; p < KCW / 2; ++p) {
             if (p < p0) continue;
             const unsigned blk = tile + p * 2048;
-            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk), v0 + p * 128);
-            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk + 1024), v1 + p * 128);
+            const unsigned o0 = PAD && kb0 + p * 128 >= kend ? OOB_OFFSET : v0 + p * 128;
+            const unsigned o1 = PAD && kb1 + p * 128 >= kend ? OOB_OFFSET : v1 + p * 128;
+            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk), o0);
+            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk + 1024), o1);
         }
     };
     issue_from(0);
@@ -340,17 +348,17 @@ __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int k
 // after one full copy is faster (163 -> 170 us when pipelined).  The layer
 // wavefront's two row blocks (17 to 32 rows in one XCD) lose with it too
 // (B = 32: 355 -> 367 us), and keep the unpipelined copy.
-template <int RB, int KCW, int NBB, int MBX>
+template <int RB, int KCW, int NBB, int MBX, bool PAD>
 __device__ __forceinline__ bool stage_dz(u32x4 rs, long r0, long ld, int kbyte, unsigned tile, const char *tilep,
                                          int lane, int valid, const u32x4 (&rf)[NBB][KCW], f32x4 (&acc)[NBB],
-                                         unsigned *flags, unsigned long long timeout, int rot)
+                                         unsigned *flags, unsigned long long timeout, int rot, int kend)
 {
     if constexpr (MBX >= 2)
-        return stage_mma_pipe<KCW, NBB, KCW / 2>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc, flags,
-                                                        timeout);
+        return stage_mma_pipe<KCW, NBB, KCW / 2, PAD>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc, flags,
+                                                      timeout, kend);
     else
-        return stage_mma_when_ready<RB, KCW, NBB>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc, flags,
-                                                  timeout, rot);
+        return stage_mma_when_ready<RB, KCW, NBB, false, PAD>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc,
+                                                              flags, timeout, rot, kend);
 }
 
 // Resident columns of a row-major bf16 matrix M [rows][ld] (R or W, whose
@@ -521,7 +529,15 @@ struct XFwdArgs {
 // (gate rows x batch rows), so each lane ends with the four gates of one
 // cell for one batch row: one 16-byte LDS store per block, and the gate math
 // reads each wave's partial sums of a cell with one 16-byte load.
-template <int HN, int MBX, bool GX16 = false, bool ACT16 = false>
+//
+// PAD: H is any multiple of 8 up to 32*HN.  The layer is treated as one of
+// 32*HN cells whose surplus weights are zero: a workgroup without cells
+// leaves at once, the resident rows and columns at or past H are zero
+// registers, and the copies read zero past a row's H elements (neighbouring
+// rows may still hold NOT_READY, a NaN).  A step costs what the full width
+// costs, set by the exchange: H = 648 at 50 rows 26.4 -> 2.1 us per forward
+// step against the generic kernel, whose grid-wide barrier alone takes 24.5 us.
+template <int HN, int MBX, bool GX16 = false, bool ACT16 = false, bool PAD = false>
 __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
 {
     constexpr int NT = 4 * HN;        // gate rows owned (i, f, g, o of HN cells)
@@ -543,6 +559,7 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
     const int j0 = slot * HN;
     const int row0 = xcd * a.RX, rowend = min(B, row0 + a.RX);
     const unsigned tile = lds_addr(&stage[w][0]);
+    if (PAD && j0 >= H) return;   // no cells: nobody waits for this workgroup
 
     // resident weights: the 4*HN rows of R feeding this workgroup's cells
     // (cell-major: row 4u + g), this wave's k range
@@ -553,13 +570,16 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
         const int g = n & 3, u = n >> 2;
         const bf16_t *rrow = a.R + (long)(g * H + j0 + u) * H + w * KW;
 #pragma unroll
-        for (int c = 0; c < KCW; ++c) rf[i][c] = ldg16(rrow + c * 32 + (lane >> 4) * 8);
+        for (int c = 0; c < KCW; ++c) {
+            const bool in = !PAD || (j0 + u < H && w * KW + c * 32 + (lane >> 4) * 8 < H);
+            rf[i][c] = in ? ldg16(rrow + c * 32 + (lane >> 4) * 8) : zero16();
+        }
     }
     const u32x4 rs_y = buffer_desc(a.y, (long)a.T * B * a.ldy * 2);
     const u32x4 rs_h0 = buffer_desc(a.h0, (long)B * H * 2);
 
-    const bool has_cell = tid < NCELL;
     const int cr = tid / HN, cu = tid % HN, cj = j0 + cu;
+    const bool has_cell = tid < NCELL && (!PAD || cj < H);
     float creg[MBX];
 #pragma unroll
     for (int mb = 0; mb < MBX; ++mb) {
@@ -599,12 +619,12 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
             const int rb0 = row0 + mb * 16;
             if (mb > 0) wait_own_lds();   // the previous block's fragment reads are done
             if (s > 0) {
-                if (!stage_mma_when_ready<RB, KCW, NB, true>(rs_y, (long)tprev * B + rb0, a.ldy, w * KW * 2, tile,
-                                                             stage[w], lane, rowend - rb0, rf, acc, a.flags, a.timeout,
-                                                             slot))
+                if (!stage_mma_when_ready<RB, KCW, NB, true, PAD>(rs_y, (long)tprev * B + rb0, a.ldy, w * KW * 2,
+                                                                  tile, stage[w], lane, rowend - rb0, rf, acc,
+                                                                  a.flags, a.timeout, slot, H * 2))
                     s_bad = 1;
             } else if (a.h0) {
-                stage_rows<RB>(rs_h0, rb0, H, w * KW * 2, tile, lane);
+                stage_rows<RB, false, false, PAD>(rs_h0, rb0, H, w * KW * 2, tile, lane, ~0u, 0, H * 2);
                 wait_own_loads();
 #pragma unroll
                 for (int c = 0; c < KCW; ++c) {
@@ -1218,7 +1238,10 @@ __device__ __forceinline__ void act_f32(const unsigned (&bits)[4], float (&v)[4]
 
 // Wave w multiplies the k range [w*H/2, (w+1)*H/2) of dh_{t-1} = R^T dz_t
 // (k over the 4H gate rows); the eight partial sums meet in LDS.
-template <int HN, int MBX, bool ACT16 = false>
+// PAD: H is any multiple of 8 up to 32*HN, as in the forward; k runs over the
+// 4H gate rows as they lie in dz, zero past them (H = 648 at 50 rows 31.5 ->
+// 2.6 us per step against the generic kernel).
+template <int HN, int MBX, bool ACT16 = false, bool PAD = false>
 __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
 {
     constexpr int NBB = HN >= 16 ? HN / 16 : 1;   // 16-column blocks of owned cells
@@ -1240,20 +1263,25 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
     const int j0 = slot * HN;
     const int row0 = xcd * a.RX, rowend = min(B, row0 + a.RX);
     const unsigned tile = lds_addr(&stage[w][0]);
+    if (PAD && j0 >= H) return;   // no cells: nobody waits for this workgroup
 
     // resident weights: rows of R^T (= columns of R) of the owned cells, this wave's k range
     u32x4 rf[NBB][KCW];
 #pragma unroll
     for (int i = 0; i < NBB; ++i) {
         const int n = i * 16 + (lane & 15);
-        const bf16_t *rrow = a.Rt + (long)(j0 + (n < HN ? n : 0)) * G4 + w * KW;
+        const bool nin = n < HN && (!PAD || j0 + n < H);
+        const bf16_t *rrow = a.Rt + (long)(j0 + (nin ? n : 0)) * G4 + w * KW;
 #pragma unroll
-        for (int c = 0; c < KCW; ++c) rf[i][c] = n < HN ? ldg16(rrow + c * 32 + (lane >> 4) * 8) : zero16();
+        for (int c = 0; c < KCW; ++c) {
+            const bool in = nin && (!PAD || w * KW + c * 32 + (lane >> 4) * 8 < 4 * H);
+            rf[i][c] = in ? ldg16(rrow + c * 32 + (lane >> 4) * 8) : zero16();
+        }
     }
     const u32x4 rs_dz = buffer_desc(a.dz, (long)a.T * B * G4 * 2);
 
-    const bool has_cell = tid < NCELL;
     const int cr = tid / HN, cu = tid % HN, cj = j0 + cu;
+    const bool has_cell = tid < NCELL && (!PAD || cj < H);
     auto load_inputs = [&](int s, BwdIn<MBX, ACT16> &in) {
         const int t = a.reverse ? a.T - 1 - s : s;
         const int tp = a.reverse ? t + 1 : t - 1;
@@ -1344,8 +1372,8 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
             f32x4 acc[NBB];
 #pragma unroll
             for (int i = 0; i < NBB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (!stage_dz<RB, KCW, NBB, MBX>(rs_dz, (long)t * B + rb0, G4, w * KW * 2, tile, stage[w], lane,
-                                             rowend - rb0, rf, acc, a.flags, a.timeout, slot))
+            if (!stage_dz<RB, KCW, NBB, MBX, PAD>(rs_dz, (long)t * B + rb0, G4, w * KW * 2, tile, stage[w], lane,
+                                                  rowend - rb0, rf, acc, a.flags, a.timeout, slot, 8 * H))
                 s_bad = 1;
 #pragma unroll
             for (int i = 0; i < NBB; ++i)
@@ -1370,7 +1398,7 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
     {
         float *dred = &red[0][0][0];                  // 16 x HN x 4 floats fit in red
         __syncthreads();
-        if (has_cell) {
+        if (tid < NCELL) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) dred[(cr * HN + cu) * 4 + g] = dbacc[g];
         }
@@ -1379,7 +1407,7 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
             const int g = tid / HN, u = tid % HN;
             float v = 0.0f;
             for (int r = 0; r < 16; ++r) v += dred[(r * HN + u) * 4 + g];
-            a.dbpart[(long)xcd * G4 + g * H + j0 + u] = v;
+            if (!PAD || j0 + u < H) a.dbpart[(long)xcd * G4 + g * H + j0 + u] = v;
         }
     }
 }
@@ -1433,9 +1461,11 @@ int g_xcd_disabled = 0;
 
 }  // namespace
 
+bool xcd_full_width(const RecShape &sh) { return sh.H == 256 || sh.H == 512 || sh.H == 1024; }
+
 bool xcd_act16(DType t, const RecShape &sh)
 {
-    if (t != DType::BF16 || sh.Hp != 0 || (sh.H != 256 && sh.H != 512 && sh.H != 1024)) return false;
+    if (t != DType::BF16 || sh.Hp != 0 || !xcd_full_width(sh)) return false;
     const int RX = (sh.B + NXCD - 1) / NXCD;
     return RX >= 5 && RX <= 32;
 }
@@ -1443,7 +1473,10 @@ bool xcd_act16(DType t, const RecShape &sh)
 bool xcd_path_ok(DType t, const RecShape &sh, int num_cus)
 {
     if (g_xcd_disabled || t != DType::BF16 || sh.Hp != 0 || num_cus != NXCD * WG_PER_XCD) return false;
-    if (sh.H != 256 && sh.H != 512 && sh.H != 1024) return false;
+    if (sh.H > 1024 || sh.H % 8 != 0) return false;
+    // the exchange copies address y and dz with 32-bit offsets in a 2 GiB descriptor
+    const long rows = (long)sh.T * sh.B;
+    if (rows * sh.ldy * 2 > 0x7fffffffL || rows * 4 * sh.H * 2 > 0x7fffffffL) return false;
     const int RX = (sh.B + NXCD - 1) / NXCD;
     return RX <= 64;
 }
@@ -1706,8 +1739,15 @@ hipError_t launch_forward_xcd(const RecShape &sh, const FwdBufs &bf, unsigned lo
     FWD_CASE(8, 1) FWD_CASE(8, 2) FWD_CASE(8, 4)
     FWD_CASE(16, 1) FWD_CASE(16, 2) FWD_CASE(16, 4)
     FWD_CASE(32, 1) FWD_CASE(32, 2) FWD_CASE(32, 4)
+#define FWD_CASE_PAD(HN_, M_) \
+    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_fwd_xcd<HN_, M_, false, false, true>>(s, &a);
+    if (a.gx) return hipErrorInvalidValue;   // the other widths keep an fp32 projection
+    FWD_CASE_PAD(8, 1) FWD_CASE_PAD(8, 2) FWD_CASE_PAD(8, 4)
+    FWD_CASE_PAD(16, 1) FWD_CASE_PAD(16, 2) FWD_CASE_PAD(16, 4)
+    FWD_CASE_PAD(32, 1) FWD_CASE_PAD(32, 2) FWD_CASE_PAD(32, 4)
 #undef FWD_CASE
 #undef FWD_CASE_ACT
+#undef FWD_CASE_PAD
     return hipErrorInvalidValue;
 }
 
@@ -1753,8 +1793,14 @@ hipError_t launch_backward_xcd(const RecShape &sh, const BwdBufs &bf, unsigned l
     BWD_CASE(8, 1) BWD_CASE(8, 2) BWD_CASE(8, 4)
     BWD_CASE(16, 1) BWD_CASE(16, 2) BWD_CASE(16, 4)
     BWD_CASE(32, 1) BWD_CASE(32, 2) BWD_CASE(32, 4)
+#define BWD_CASE_PAD(HN_, M_) \
+    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_bwd_xcd<HN_, M_, false, true>>(s, &a);
+    BWD_CASE_PAD(8, 1) BWD_CASE_PAD(8, 2) BWD_CASE_PAD(8, 4)
+    BWD_CASE_PAD(16, 1) BWD_CASE_PAD(16, 2) BWD_CASE_PAD(16, 4)
+    BWD_CASE_PAD(32, 1) BWD_CASE_PAD(32, 2) BWD_CASE_PAD(32, 4)
 #undef BWD_CASE
 #undef BWD_CASE_ACT
+#undef BWD_CASE_PAD
     return hipErrorInvalidValue;
 }
 
