@@ -183,7 +183,7 @@ extern "C" lstm_status_t lstm_create(const lstm_desc_t *desc, lstm_handle_t *out
         h->w_dhn = o;  o = align256(o + (size_t)d.B * d.H * 4);
         {
             size_t pf = colsum_partial_floats((int)TB, (int)G4);
-            if (pf < (size_t)8 * G4) pf = (size_t)8 * G4;   // per-XCD bias partials
+            if (pf < (size_t)MAX_BGROUPS * G4) pf = (size_t)MAX_BGROUPS * G4;   // bias partials of the recurrences
             h->w_part = o; o = align256(o + pf * 4);
         }
         // split-K partials of the weight- and input-gradient products
@@ -668,6 +668,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
         RecShape sh{T, B, I, H, Hp, d.reverse, h->ldy};
         const bool xcd = use_xcd(h, sh);
         const bool stepwise = !xcd && use_stepwise(h, h->bwd_ok);
+        const int db_rows = xcd ? 8 : h->bwd.bgroups;   // partial bias gradients of a persistent recurrence
 
         BwdBufs bb{};
         bb.Rt = Rt; bb.Pt = Pt; bb.dy = dy; bb.dhT = dhT; bb.dcT = dcT; bb.h0 = h0; bb.c0 = c0;
@@ -723,9 +724,9 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
             }
             g.hlen = B;
             g.C2 = dR; g.ldc2 = Hr;
-            if (xcd) {   // db = sum of the recurrence's per-XCD partials, done by the same launch
+            if (!stepwise) {   // db = sum of the recurrence's partials, done by the same launch
                 g.side.sum_src = reinterpret_cast<const float *>(wv + h->w_part);
-                g.side.sum_rows = 8;
+                g.side.sum_rows = db_rows;
                 g.side.sum_cols = (int)G4;
                 g.side.sum_dst = db;
                 g.side.sum_acc = accumulate;
@@ -775,9 +776,10 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
             }
             if (!beta) TRY_HIP("dR zero", fill_u32(dR, (size_t)G4 * Hr, 0u, s));
         }
-        if (xcd) {   // the recurrence left one fp32 partial per XCD (the fused product sums them itself)
+        if (!stepwise) {   // fp32 partials per XCD or batch group (the fused product sums them itself)
             if (!fused)
-                TRY_HIP("db", sum_rows(reinterpret_cast<const float *>(wv + h->w_part), 8, (int)G4, db, accumulate, s));
+                TRY_HIP("db", sum_rows(reinterpret_cast<const float *>(wv + h->w_part), db_rows, (int)G4, db,
+                                       accumulate, s));
         } else
             TRY_HIP("db", colsum(h->dt, dz, (int)TB, (int)G4, reinterpret_cast<float *>(wv + h->w_part), db, accumulate, s));
         if (Hp) {  // dP = sum_t dh_t^T m_t

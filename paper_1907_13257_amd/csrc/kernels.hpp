@@ -211,7 +211,7 @@ struct BwdBufs {
     float *dhn;         // [B][H] carry of dh between steps (plain LSTM)
     void *dh0;
     float *dc0;
-    float *dbpart;      // XCD-local kernel: [8][4H] per-XCD partial bias gradients
+    float *dbpart;      // partial bias gradients: [8][4H] per XCD (XCD-local), [bgroups][4H] (generic)
     unsigned *sync;
 };
 hipError_t launch_backward(DType t, const RecShape &sh, const RecTiling &tl, const BwdBufs &b, hipStream_t s);
@@ -219,9 +219,10 @@ hipError_t launch_backward(DType t, const RecShape &sh, const RecTiling &tl, con
 // Workspace layout of the sync block (u32 words); the words a kernel uses are
 // zeroed before it is launched.
 constexpr size_t SYNC_BYTES = 4096;
-constexpr int SYNC_COUNT0 = 0;     // barrier counter of the generic kernels
-constexpr int SYNC_ABORT = 64;     // abort flag of the generic kernels
-constexpr int SYNC_WORDS = 128;    // words cleared before a generic launch
+constexpr int SYNC_ABORT = 0;      // abort word of the generic kernels
+constexpr int SYNC_FLAGS = 4;      // their step flags: per batch group one word per workgroup, in whole 16 bytes
+constexpr int SYNC_WORDS = 512;    // words cleared before a generic launch
+constexpr int MAX_BGROUPS = 16;    // batch groups of a generic launch: at most 256 + 3 * 16 flag words
 constexpr int XCD_FLAGS = 256;     // words of the XCD-local kernels (257 words)
 constexpr int XCD_CLAIM = 0;       // 8 per-XCD masks of claimed workgroup slots, relative to XCD_FLAGS
 constexpr int XCD_ABORT = 256;     // abort flag, relative to XCD_FLAGS

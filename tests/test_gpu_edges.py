@@ -47,3 +47,32 @@ def test_padded_xcd_widths(T, B, H, reverse, states):
     gpu = run_case(T, B, 40, H, 0, "bf16", reverse, H ** -0.5, states)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert gpu["tiling"][3] == 1001 and gpu["tiling"][7] == 1001, gpu["tiling"]
+
+
+# Generic persistent kernels (fp32, LSTMP, bf16 wider than 1024): (T, B, I, H,
+# Hp, dtype, reverse, states).  Between them the planned tilings have 1 and 2
+# row blocks per tile and several tiles per workgroup, weights in LDS and
+# streamed, projections with fewer and with more column blocks than workgroups.
+GENERIC_CASES = [
+    (3, 1, 8, 8, 0, "f32", False, True),
+    (4, 16, 24, 256, 0, "f32", True, True),       # whole tiles
+    (3, 33, 24, 264, 0, "f32", False, False),     # one row past two row blocks, half a chunk of k
+    (2, 150, 16, 72, 0, "f32", True, True),       # ten row blocks
+    (2, 530, 16, 136, 0, "f32", False, True),     # several tiles per workgroup: carries through memory
+    (3, 20, 16, 1024, 0, "f32", False, True),     # full-width fp32
+    (2, 18, 16, 1160, 0, "f32", True, True),      # weights of a backward slice beyond LDS: streamed
+    (3, 17, 16, 1032, 0, "bf16", False, True),    # bf16 just past the XCD-local widths
+    (2, 70, 16, 1544, 0, "bf16", True, True),
+    (3, 6, 16, 40, 8, "f32", False, True),        # LSTMP: half a column block
+    (3, 40, 24, 16, 200, "bf16", True, True),     # more column blocks than workgroups
+    (3, 65, 24, 520, 136, "bf16", False, False),
+    (2, 19, 24, 1800, 256, "bf16", False, True),
+    (2, 36, 24, 640, 320, "f32", True, True),
+    (3, 300, 24, 64, 32, "bf16", False, True),    # several tiles per workgroup
+]
+
+
+@pytest.mark.parametrize("T,B,I,H,Hp,dtype,reverse,states", GENERIC_CASES)
+def test_generic_kernels(T, B, I, H, Hp, dtype, reverse, states):
+    gpu = run_case(T, B, I, H, Hp, dtype, reverse, min(0.3, H ** -0.5), states)
+    assert gpu["tiling"][3] not in (1000, 1001, 2000), gpu["tiling"]
