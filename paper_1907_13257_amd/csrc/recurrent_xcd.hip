@@ -240,6 +240,130 @@ __device__ __forceinline__ u32x4 pair_frag(const char *tilep, int c, int lane)
     return *reinterpret_cast<const u32x4 *>(tilep + (c >> 1) * 2048 + i * 128 + ((piece ^ ((i >> 1) & 7)) * 16));
 }
 
+// Pipelined row blocks.  With three or four 16-row blocks per XCD a block's
+// rows are exchanged two blocks before they are needed, so their copy is issued
+// while the block before is still worked on: forward, as soon as its fragments
+// are read (the wave's LDS tile is then free), backward, pair by pair during
+// its product; they land while its partial sums are reduced and its gate math
+// runs.  Per layer, T = 50, H = 1024: B = 512 forward 604 -> 440 us, backward
+// 733 -> 615 us; B = 264 (three blocks, the fourth not run) 480 -> 320 us and
+// 582 -> 400 us.  With two blocks the rows are not there in time (forward 237
+// -> 249 us at B = 256), so those copy at the start of their own block.  What
+// bounds a block now: forward, in cycles of about 4900, the matrix cores 1024
+// of 1450-1950 spent on the product, 512 each writing and reading the partial
+// sums, and the barriers' skew; backward the copy, 128 KiB at the CU's 64
+// bytes per cycle, 2048 of about 6500.
+// PipeRows and PipePairs hold the two copy forms (the forward's slice of 256
+// bytes per row, the backward's of 1 KiB), multiply_landed the product of a
+// slice that has landed.
+
+// 16 rows in the layout of stage_rows.
+template <int RB, int KCW, bool PAD>
+struct PipeRows {
+    u32x4 rs;
+    long ld;
+    int kbyte, lane, rot, kend;
+    unsigned tile;
+    const char *tilep;
+    __device__ __forceinline__ void issue(long r0, int valid) const
+    {
+        constexpr int RPI = 1024 / RB;
+        unsigned qmask = 0;   // only the instructions that cover valid rows
+#pragma unroll
+        for (int q = 0; q < 16 / RPI; ++q)
+            if (q * RPI < valid) qmask |= 1u << q;
+        stage_rows<RB, true, true, PAD>(rs, r0, ld, kbyte, tile, lane, qmask, rot, kend);
+    }
+    __device__ __forceinline__ u32x4 frag(int c) const { return stage_frag<RB>(tilep, c, lane); }
+};
+
+// 16 rows in chunk pairs (pair_voff, pair_frag).  LDS block p holds pair
+// p ^ pperm of the slice (and the caller's weights are loaded in that order).
+// Rows of dz lie 8 KiB apart at H = 1024, a multiple of the L2's channel
+// interleave: one pair of all rows and waves falls in 4 of the 16 channels, so
+// the workgroups of an XCD, which copy the same rows at the same time, take
+// their pairs in different orders (pperm from the slot; B = 512 backward 662 ->
+// 611 us per layer, B = 256 305 -> 297 us).
+template <int KCW, bool PAD>
+struct PipePairs {
+    u32x4 rs;
+    long ld;
+    int kbyte, lane, kend, pperm;
+    unsigned tile;
+    const char *tilep;
+    // one chunk pair; v0, v1: pair_voff of its two instructions
+    __device__ __forceinline__ void issue_pair(int p, unsigned v0, unsigned v1) const
+    {
+        // PAD: first byte of this lane's piece of pair 0 within the row, per instruction
+        const int kb0 = kbyte + ((lane & 7) ^ ((lane >> 4) & 7)) * 16;
+        const int kb1 = kbyte + ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) * 16;
+        const unsigned blk = tile + p * 2048;
+        const int pb = (p ^ pperm) * 128;
+        const unsigned o0 = PAD && kb0 + pb >= kend ? OOB_OFFSET : v0 + pb;
+        const unsigned o1 = PAD && kb1 + pb >= kend ? OOB_OFFSET : v1 + pb;
+        dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk), o0);
+        dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk + 1024), o1);
+    }
+    __device__ __forceinline__ void issue(long r0, int valid) const
+    {
+        const unsigned v0 = pair_voff(r0, ld, kbyte, lane, 0, valid);
+        const unsigned v1 = pair_voff(r0, ld, kbyte, lane, 1, valid);
+#pragma unroll
+        for (int p = 0; p < KCW / 2; ++p) issue_pair(p, v0, v1);
+    }
+    __device__ __forceinline__ u32x4 frag(int c) const { return pair_frag(tilep, c, lane); }
+};
+
+// acc[i] = (the slice in the wave's tile) x rf[i] (WT: the transposed
+// product), the slice copied by cp.issue(r0, valid) and landed.  While an
+// element of the first `valid` rows still holds NOT_READY the copy and the
+// product are repeated.  Returns false as stage_mma_when_ready does.
+template <bool WT, int KCW, int NBX, typename CP>
+__device__ __forceinline__ bool multiply_landed(const CP &cp, long r0, int valid, const u32x4 (&rf)[NBX][KCW],
+                                                f32x4 (&acc)[NBX], unsigned *flags, unsigned long long timeout)
+{
+    const int lane = cp.lane;
+    const bool row_in = (lane & 15) < valid;
+    unsigned long long t0 = 0;
+    bool waited = false;
+    while (true) {
+#pragma unroll
+        for (int i = 0; i < NBX; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        u16x2 seen = {0, 0};
+#pragma unroll
+        for (int c = 0; c < KCW; ++c) {
+            // fragments in flight at most four chunks ahead (bounded registers)
+            if (c % 4 == 0 && c > 0) __builtin_amdgcn_sched_barrier(0);
+            const u32x4 fa = cp.frag(c);
+            seen = max_halves(seen, fa);
+#pragma unroll
+            for (int i = 0; i < NBX; ++i) {
+                if (WT)
+                    mfma16(acc[i], rf[i][c], fa, bf16_t{});
+                else
+                    mfma16(acc[i], fa, rf[i][c], bf16_t{});
+            }
+        }
+        if (__builtin_amdgcn_ballot_w64(saw_not_ready(seen) && row_in) == 0) return true;
+        if (!waited) {
+            t0 = wall_clock64();
+            waited = true;
+        }
+        wait_own_lds();   // the fragments are in registers before the tile is overwritten
+        cp.issue(r0, valid);
+        const unsigned ab = __builtin_amdgcn_raw_buffer_load_b32(rsrc(flags), XCD_ABORT * 4, 0, 16);
+        wait_own_loads();
+        if (ab != 0) return false;
+        if (wall_clock64() - t0 > timeout) {
+            if (lane == 0) {
+                __hip_atomic_fetch_or(&g_xcd_tripped, TRIP_WATCHDOG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(flags + XCD_ABORT, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            return false;
+        }
+    }
+}
+
 // s_waitcnt vmcnt(n), n in [0, 15]; n is a constant once the caller's loop
 // is unrolled, and the switch folds to the one instruction.
 __device__ __forceinline__ void wait_loads_upto(int n)
@@ -258,37 +382,33 @@ __device__ __forceinline__ void wait_loads_upto(int n)
 #undef LSTM355_VMCNT
 }
 
-// The pipelined form of stage_mma_when_ready (untransposed product): all
-// copies are issued at once (two instructions per chunk pair, KCW in all);
-// each group of G chunks is multiplied as soon as its own copies have landed
-// and none of its valid elements holds NOT_READY.  A group that saw one is copied again together
-// with every later pair (they were copied at the same time, so they are
-// likely stale too), until it is complete.  Chunks are multiplied in order,
-// so the sums are those of the unpipelined form, bit for bit.
-template <int KCW, int NBX, int G, bool PAD = false>
-__device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int kbyte, unsigned tile,
-                                               const char *tilep, int lane, int valid,
-                                               const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX], unsigned *flags,
-                                               unsigned long long timeout, int kend = 0)
+// Two row blocks per XCD, backward: copies and multiplies a block's slice in
+// two halves.  All copies are issued at once (two instructions per chunk pair,
+// KCW in all); a half is multiplied as soon as its own copies have landed and
+// none of its valid elements holds NOT_READY, the first while the second still
+// lands.  A half that saw one is copied again together with every later pair
+// (they were copied at the same time, so they are likely stale too).  With
+// two blocks the copy of a block one block ahead (multiply_and_issue) finds
+// rows missing too often: B = 256 313 us per layer this way, 389 us that way;
+// with one block, re-copying just the missing rows after one full copy
+// (stage_mma_when_ready) is faster (163 us against 170 us in halves at B =
+// 128), and the layer wavefront's two blocks lose with halves as well (B = 32:
+// 355 -> 367 us).
+template <int KCW, int NBX, bool PAD>
+__device__ __forceinline__ bool multiply_halves(const PipePairs<KCW, PAD> &cp, long r0, int valid,
+                                                const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX], unsigned *flags,
+                                                unsigned long long timeout)
 {
-    static_assert(KCW >= 2 && KCW <= 16 && KCW % 2 == 0, "whole chunk pairs, at most 16 instructions in flight");
-    static_assert(G % 2 == 0 && KCW % G == 0, "whole pairs per group, whole groups");
-    const unsigned v0 = pair_voff(r0, ld, kbyte, lane, 0, valid);
-    const unsigned v1 = pair_voff(r0, ld, kbyte, lane, 1, valid);
+    constexpr int G = KCW / 2;
+    static_assert(KCW >= 4 && KCW <= 16 && G % 2 == 0, "whole chunk pairs per half, at most 16 instructions in flight");
+    const int lane = cp.lane;
+    const unsigned v0 = pair_voff(r0, cp.ld, cp.kbyte, lane, 0, valid);
+    const unsigned v1 = pair_voff(r0, cp.ld, cp.kbyte, lane, 1, valid);
     const bool row_in = (lane & 15) < valid;
-    // PAD: first byte of this lane's piece of pair 0 within the row, per instruction
-    const int kb0 = kbyte + ((lane & 7) ^ ((lane >> 4) & 7)) * 16;
-    const int kb1 = kbyte + ((lane & 7) ^ ((4 + (lane >> 4)) & 7)) * 16;
     auto issue_from = [&](int p0) {
 #pragma unroll
-        for (int p = 0; p < KCW / 2; ++p) {
-            if (p < p0) continue;
-            const unsigned blk = tile + p * 2048;
-            const unsigned o0 = PAD && kb0 + p * 128 >= kend ? OOB_OFFSET : v0 + p * 128;
-            const unsigned o1 = PAD && kb1 + p * 128 >= kend ? OOB_OFFSET : v1 + p * 128;
-            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk), o0);
-            dma16_sc1(rs, __builtin_amdgcn_readfirstlane(blk + 1024), o1);
-        }
+        for (int p = 0; p < KCW / 2; ++p)
+            if (p >= p0) cp.issue_pair(p, v0, v1);
     };
     issue_from(0);
 #pragma unroll
@@ -304,7 +424,7 @@ __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int k
         u16x2 seen = {0, 0};
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            fa[g] = pair_frag(tilep, c0 + g, lane);
+            fa[g] = cp.frag(c0 + g);
             seen = max_halves(seen, fa[g]);
         }
         while (__builtin_amdgcn_ballot_w64(saw_not_ready(seen) && row_in) != 0) {
@@ -317,8 +437,7 @@ __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int k
             if (ab != 0) return false;
             if (wall_clock64() - t0 > timeout) {
                 if (lane == 0) {
-                    __hip_atomic_fetch_or(&g_xcd_tripped, TRIP_WATCHDOG, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_or(&g_xcd_tripped, TRIP_WATCHDOG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(flags + XCD_ABORT, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 return false;
@@ -329,7 +448,7 @@ __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int k
             seen = u16x2{0, 0};
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                fa[g] = pair_frag(tilep, c0 + g, lane);
+                fa[g] = cp.frag(c0 + g);
                 seen = max_halves(seen, fa[g]);
             }
         }
@@ -341,24 +460,60 @@ __device__ __forceinline__ bool stage_mma_pipe(u32x4 rs, long r0, long ld, int k
     return true;
 }
 
-// The dz rows of a BPTT step times the resident R^T rows, for the per-layer
-// backward.  With two or more row blocks per XCD the copy is pipelined in two
-// halves (GNMT-4, B = 256: 336 -> 307 us per layer); with one, the first copy
-// usually finds rows still missing, and re-copying just the missing rows
-// after one full copy is faster (163 -> 170 us when pipelined).  The layer
-// wavefront's two row blocks (17 to 32 rows in one XCD) lose with it too
-// (B = 32: 355 -> 367 us), and keep the unpipelined copy.
-template <int RB, int KCW, int NBB, int MBX, bool PAD>
-__device__ __forceinline__ bool stage_dz(u32x4 rs, long r0, long ld, int kbyte, unsigned tile, const char *tilep,
-                                         int lane, int valid, const u32x4 (&rf)[NBB][KCW], f32x4 (&acc)[NBB],
-                                         unsigned *flags, unsigned long long timeout, int rot, int kend)
+// multiply_landed with the copy of the next block's rows (from nr0, nvalid of
+// them, when `next`) spread over the product: a chunk pair's copy is issued as
+// soon as its fragments are in registers.  The copies run at the CU's 64 bytes
+// per cycle (2048 cycles for the backward's 128 KiB) while the matrix cores
+// work, instead of after them.  An incomplete block is copied again, then the
+// next block's rows once more.
+template <int KCW, int NBX, bool PAD>
+__device__ __forceinline__ bool multiply_and_issue(const PipePairs<KCW, PAD> &cp, long r0, int valid,
+                                                   const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX], unsigned *flags,
+                                                   unsigned long long timeout, bool next, long nr0, int nvalid)
 {
-    if constexpr (MBX >= 2)
-        return stage_mma_pipe<KCW, NBB, KCW / 2, PAD>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc, flags,
-                                                      timeout, kend);
-    else
-        return stage_mma_when_ready<RB, KCW, NBB, false, PAD>(rs, r0, ld, kbyte, tile, tilep, lane, valid, rf, acc,
-                                                              flags, timeout, rot, kend);
+    constexpr int G = 4;   // chunks per group: their fragments are read one group ahead
+    static_assert(KCW % G == 0, "whole groups");
+    const int lane = cp.lane;
+    const unsigned v0 = pair_voff(nr0, cp.ld, cp.kbyte, lane, 0, nvalid);
+    const unsigned v1 = pair_voff(nr0, cp.ld, cp.kbyte, lane, 1, nvalid);
+#pragma unroll
+    for (int i = 0; i < NBX; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u16x2 seen = {0, 0};
+    u32x4 fa[2][G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) fa[0][g] = cp.frag(g);
+#pragma unroll
+    for (int c0 = 0; c0 < KCW; c0 += G) {
+        u32x4 (&cur)[G] = fa[(c0 / G) & 1];
+        if (c0 + G < KCW) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) fa[(c0 / G + 1) & 1][g] = cp.frag(c0 + G + g);
+            asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");   // this group's fragments are in registers
+        } else {
+            wait_own_lds();
+        }
+        if (next) {
+#pragma unroll
+            for (int p = 0; p < G / 2; ++p) cp.issue_pair(c0 / 2 + p, v0, v1);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            seen = max_halves(seen, cur[g]);
+#pragma unroll
+            for (int i = 0; i < NBX; ++i) mfma16(acc[i], cur[g], rf[i][c0 + g], bf16_t{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (__builtin_amdgcn_ballot_w64(saw_not_ready(seen) && (lane & 15) < valid) == 0) return true;
+    wait_own_loads();
+    cp.issue(r0, valid);
+    wait_own_loads();
+    if (!multiply_landed<false, KCW, NBX>(cp, r0, valid, rf, acc, flags, timeout)) return false;
+    if (next) {
+        wait_own_lds();
+        cp.issue(nr0, nvalid);
+    }
+    return true;
 }
 
 // Resident columns of a row-major bf16 matrix M [rows][ld] (R or W, whose
@@ -580,15 +735,148 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
 
     const int cr = tid / HN, cu = tid % HN, cj = j0 + cu;
     const bool has_cell = tid < NCELL && (!PAD || cj < H);
+    __shared__ int s_bad;
+    if (tid == 0) s_bad = 0;   // ordered by the first barrier below
+
+    if constexpr (MBX > 2) {
+        // Pipelined row blocks: see PipeRows.  The input projection of a block
+        // is loaded one block ahead, before the copy of that block's rows.
+        const PipeRows<RB, KCW, PAD> cp{rs_y, a.ldy, w * KW * 2, lane, slot, H * 2, tile, stage[w]};
+        auto load_gx = [&](int s, int b, unsigned (&g4)[4]) {
+            const int t = a.reverse ? a.T - 1 - s : s;
+            const bool v = has_cell && b < rowend;
+            const long e = ((long)t * B + b) * G4 + cj;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if constexpr (GX16)
+                    g4[g] = v ? (unsigned)a.gx[e + g * H] : 0u;
+                else
+                    g4[g] = v ? __float_as_uint(a.gates[e + g * H]) : 0u;
+            }
+        };
+        // h_t of a cell, and what the backward needs of it (not on the critical path)
+        auto store_cell = [&](int s, int b, float ig, float fg, float gg, float og, float c, float m) {
+            const int t = a.reverse ? a.T - 1 - s : s;
+            const bool last = s == a.T - 1;
+            const long row = (long)t * B + b;
+            const bf16_t hv = ready_value(f32_to_bf16(m));
+            a.y[row * a.ldy + cj] = hv;
+            if (last && a.hT) a.hT[(long)b * H + cj] = hv;
+            if constexpr (ACT16) {
+                f16_t *ap = a.act + row * G4 + cj;
+                ap[0] = (f16_t)ig;
+                ap[H] = (f16_t)fg;
+                ap[2 * H] = (f16_t)gg;
+                ap[3 * H] = (f16_t)og;
+            } else {
+                float *gp = a.gates + row * G4 + cj;
+                gp[0] = ig;
+                gp[H] = fg;
+                gp[2 * H] = gg;
+                gp[3 * H] = og;
+            }
+            a.cs[row * H + cj] = c;
+            if (last && a.cT) a.cT[(long)b * H + cj] = c;
+        };
+        // pre-activations of a cell: its input projection (in the bits it was
+        // loaded) plus the waves' partial sums of row r
+        auto cell_z = [&](const unsigned (&g4)[4], int r, float (&z)[4]) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if constexpr (GX16) {
+                    unsigned u = g4[g];
+                    // the conversion stays here: hoisted next to its load it
+                    // would make that load's wait a full memory latency
+                    asm volatile("" : "+v"(u));
+                    z[g] = to_f32(__builtin_bit_cast(f16_t, (uint16_t)u));
+                } else {
+                    z[g] = __uint_as_float(g4[g]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const f32x4 p = *reinterpret_cast<const f32x4 *>(&red[q][r][4 * cu]);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) z[g] += p[g];
+            }
+        };
+        const int nblk = rowend > row0 ? (rowend - row0 + 15) / 16 : 0;
+        __shared__ float creg[MBX][XT];   // cell states, each thread its own element
+        for (int mb = 0; mb < MBX; ++mb) {
+            const int b = row0 + mb * 16 + cr;
+            creg[mb][tid] = (has_cell && b < rowend && a.c0) ? a.c0[(long)b * H + cj] : 0.0f;
+        }
+        unsigned gx[4], gxn[4] = {0u, 0u, 0u, 0u};
+        load_gx(0, row0 + cr, gx);
+        for (int s = 0; s < a.T; ++s) {
+            const int t = a.reverse ? a.T - 1 - s : s;
+            const int tp = a.reverse ? t + 1 : t - 1;
+#pragma unroll 1
+            for (int mb = 0; mb < nblk; ++mb) {
+                const int rb0 = row0 + mb * 16;
+                const bool wrap = mb + 1 >= nblk;
+                const int ns = wrap ? s + 1 : s, nrb0 = wrap ? row0 : rb0 + 16;
+                f32x4 acc[NB];
+#pragma unroll
+                for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (s > 0) {
+                    if (!multiply_landed<true, KCW, NB>(cp, (long)tp * B + rb0, rowend - rb0, rf, acc, a.flags,
+                                                        a.timeout))
+                        s_bad = 1;
+                } else if (a.h0) {
+                    wait_own_lds();
+                    stage_rows<RB, false, false, PAD>(rs_h0, rb0, H, w * KW * 2, tile, lane, ~0u, 0, H * 2);
+                    wait_own_loads();
+#pragma unroll
+                    for (int c = 0; c < KCW; ++c) {
+                        const u32x4 fa = stage_frag<RB>(stage[w], c, lane);
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) mfma16(acc[i], rf[i][c], fa, bf16_t{});
+                    }
+                }
+                // the next block: its input projection, and its rows now that this block's fragments are read
+                if (ns < a.T) {
+                    load_gx(ns, nrb0 + cr, gxn);
+                    if (ns > 0) {
+                        const int ntp = a.reverse ? a.T - ns : ns - 1;
+                        wait_own_lds();
+                        cp.issue((long)ntp * B + nrb0, rowend - nrb0);
+                    }
+                }
+                // lane: batch row lane%16, gates 0..3 of cell 4i + lane/16 of block i
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    *reinterpret_cast<f32x4 *>(&red[w][lane & 15][i * 16 + 4 * (lane >> 4)]) = acc[i];
+                __syncthreads();
+                if (s_bad) {   // the same decision in every wave
+                    wait_own_loads();
+                    return;
+                }
+                float z[4];
+                cell_z(gx, has_cell ? cr : 0, z);
+                const float ig = sigmoid_f(z[0]), fg = sigmoid_f(z[1]), gg = tanh_f(z[2]), og = sigmoid_f(z[3]);
+                const float c = fg * creg[mb][tid] + ig * gg;
+                const float m = og * tanh_f(c);
+                creg[mb][tid] = c;
+                // the next block's rows and input projection have landed (before
+                // this block's stores, so that the wait does not cover them)
+                wait_own_loads();
+                asm volatile("" : "+v"(gxn[0]), "+v"(gxn[1]), "+v"(gxn[2]), "+v"(gxn[3]));
+#pragma unroll
+                for (int g = 0; g < 4; ++g) gx[g] = gxn[g];
+                if (has_cell && rb0 + cr < rowend) store_cell(s, rb0 + cr, ig, fg, gg, og, c, m);
+                __syncthreads();   // red is rewritten by the next block
+            }
+        }
+        return;
+    }
+
     float creg[MBX];
 #pragma unroll
     for (int mb = 0; mb < MBX; ++mb) {
         const int b = row0 + mb * 16 + cr;
         creg[mb] = (has_cell && b < rowend && a.c0) ? a.c0[(long)b * H + cj] : 0.0f;
     }
-
-    __shared__ int s_bad;
-    if (tid == 0) s_bad = 0;   // ordered by the first barrier below
 
     int tprev = 0;
     for (int s = 0; s < a.T; ++s) {
@@ -644,12 +932,10 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
             // values nobody stores) and only the stores depend on the lane:
             // the input projection loaded for this step is then consumed on
             // every path, and the next step's loads do not wait for these
-            // loads, nor for the stores issued after them.  With four row
-            // blocks the registers run short and the lanes without a row skip it.
-            constexpr bool ALL_LANES = MBX <= 2;
+            // loads, nor for the stores issued after them.
             const int b = rb0 + cr;
             const int crr = has_cell ? cr : 0;
-            if (ALL_LANES || (has_cell && b < rowend)) {
+            {
                 float z[4];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -1217,11 +1503,11 @@ struct XBwdArgs {
 // converting them where they are loaded would make the wave wait for those
 // loads, and with them for the dz stores issued before, ahead of the
 // exchange copy.
-template <int MBX, bool ACT16>
+template <bool ACT16>
 struct BwdIn {
-    bf16_t dy[MBX];
-    typename std::conditional<ACT16, unsigned, float>::type g[MBX][4];   // fp16 bit patterns or fp32
-    float c[MBX], cp[MBX];
+    bf16_t dy;
+    typename std::conditional<ACT16, unsigned, float>::type g[4];   // fp16 bit patterns or fp32
+    float c, cp;
 };
 
 // Four fp16 activations from their bit patterns, converted where they are
@@ -1265,7 +1551,9 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
     const unsigned tile = lds_addr(&stage[w][0]);
     if (PAD && j0 >= H) return;   // no cells: nobody waits for this workgroup
 
-    // resident weights: rows of R^T (= columns of R) of the owned cells, this wave's k range
+    // resident weights: rows of R^T (= columns of R) of the owned cells, this
+    // wave's k range (in the order of PipePairs with two or more row blocks)
+    const int pperm = MBX >= 2 ? slot & (KCW / 2 - 1) : 0;
     u32x4 rf[NBB][KCW];
 #pragma unroll
     for (int i = 0; i < NBB; ++i) {
@@ -1274,124 +1562,203 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
         const bf16_t *rrow = a.Rt + (long)(j0 + (nin ? n : 0)) * G4 + w * KW;
 #pragma unroll
         for (int c = 0; c < KCW; ++c) {
-            const bool in = nin && (!PAD || w * KW + c * 32 + (lane >> 4) * 8 < 4 * H);
-            rf[i][c] = in ? ldg16(rrow + c * 32 + (lane >> 4) * 8) : zero16();
+            const int kc = (c ^ (2 * pperm)) * 32 + (lane >> 4) * 8;
+            const bool in = nin && (!PAD || w * KW + kc < 4 * H);
+            rf[i][c] = in ? ldg16(rrow + kc) : zero16();
         }
     }
     const u32x4 rs_dz = buffer_desc(a.dz, (long)a.T * B * G4 * 2);
 
     const int cr = tid / HN, cu = tid % HN, cj = j0 + cu;
     const bool has_cell = tid < NCELL && (!PAD || cj < H);
-    auto load_inputs = [&](int s, BwdIn<MBX, ACT16> &in) {
+    auto load_inputs = [&](int s, int b, BwdIn<ACT16> &in) {
         const int t = a.reverse ? a.T - 1 - s : s;
         const int tp = a.reverse ? t + 1 : t - 1;
+        const bool v = has_cell && b < rowend;
+        const long rt = (long)t * B + (v ? b : 0);
+        in.dy = v ? a.dy[rt * a.ldy + cj] : (bf16_t)0;
 #pragma unroll
-        for (int mb = 0; mb < MBX; ++mb) {
-            const int b = row0 + mb * 16 + cr;
-            const bool v = has_cell && b < rowend;
-            const long rt = (long)t * B + (v ? b : 0);
-            in.dy[mb] = v ? a.dy[rt * a.ldy + cj] : (bf16_t)0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if constexpr (ACT16)
-                    in.g[mb][g] = v ? (unsigned)a.act[rt * G4 + g * H + cj] : 0u;
-                else
-                    in.g[mb][g] = v ? a.gates[rt * G4 + g * H + cj] : 0.0f;
-            }
-            in.c[mb] = v ? a.cs[rt * H + cj] : 0.0f;
-            in.cp[mb] = (v && s > 0) ? a.cs[((long)tp * B + b) * H + cj]
-                                     : ((v && a.c0) ? a.c0[(long)(v ? b : 0) * H + cj] : 0.0f);
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (ACT16)
+                in.g[g] = v ? (unsigned)a.act[rt * G4 + g * H + cj] : 0u;
+            else
+                in.g[g] = v ? a.gates[rt * G4 + g * H + cj] : 0.0f;
         }
+        in.c = v ? a.cs[rt * H + cj] : 0.0f;
+        in.cp = (v && s > 0) ? a.cs[((long)tp * B + b) * H + cj]
+                             : ((v && a.c0) ? a.c0[(long)(v ? b : 0) * H + cj] : 0.0f);
     };
 
-    float dhn[MBX], dcn[MBX];
     float dbacc[4] = {0.f, 0.f, 0.f, 0.f};   // this thread's rows, summed over steps
-#pragma unroll
-    for (int mb = 0; mb < MBX; ++mb) {
-        const int b = row0 + mb * 16 + cr;
-        const bool v = has_cell && b < rowend;
-        dhn[mb] = (v && a.dhT) ? to_f32(a.dhT[(long)b * H + cj]) : 0.0f;
-        dcn[mb] = (v && a.dcT) ? a.dcT[(long)b * H + cj] : 0.0f;
-    }
-    BwdIn<MBX, ACT16> in;
-    load_inputs(a.T - 1, in);
+    auto dh_init = [&](int b) {
+        return (has_cell && b < rowend && a.dhT) ? to_f32(a.dhT[(long)b * H + cj]) : 0.0f;
+    };
+    auto dc_init = [&](int b) { return (has_cell && b < rowend && a.dcT) ? a.dcT[(long)b * H + cj] : 0.0f; };
     __shared__ int s_bad;
     if (tid == 0) s_bad = 0;   // ordered by the first barrier below
 
-    for (int s = a.T - 1; s >= 0; --s) {
+    // Gate gradients of one cell, from its inputs and the carries dh and
+    // dc (replaced by the carry to the step before); z: the four before rounding.
+    auto gate_grads = [&](const BwdIn<ACT16> &in, float dh, float &dc, float (&z)[4]) {
+        float gv[4];
+        if constexpr (ACT16) {
+            act_f32(in.g, gv);
+        } else {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) gv[g] = in.g[g];
+        }
+        const float ig = gv[0], fg = gv[1], gg = gv[2], og = gv[3];
+        const float dm = to_f32(in.dy) + dh;
+        const float tc = tanh_f(in.c);
+        const float d_o = dm * tc;
+        const float d_c = dc + dm * og * (1.0f - tc * tc);
+        const float d_i = d_c * gg, d_g = d_c * ig, d_f = d_c * in.cp;
+        z[0] = d_i * ig * (1.0f - ig);
+        z[1] = d_f * fg * (1.0f - fg);
+        z[2] = d_g * (1.0f - gg * gg);
+        z[3] = d_o * og * (1.0f - og);
+        dc = d_c * fg;
+    };
+    auto store_dz = [&](int s, int b, const float (&z)[4], float dc) {
         const int t = a.reverse ? a.T - 1 - s : s;
-        // gate gradients of the owned cells.  Every lane computes them (lanes
-        // without a cell or row loaded zeros) and only the stores depend on
-        // the lane: each prefetched input is then consumed on every path, and
-        // the next prefetch does not wait for the previous one (nor for the
-        // dz stores issued after it) before the exchange copy.  With four row
-        // blocks the registers run short and the lanes without a row skip it.
-        constexpr bool ALL_LANES = MBX <= 2;
+        const bool v = has_cell && b < rowend;
+        if (v) {
+            bf16_t *dzp = a.dz + ((long)t * B + b) * G4 + cj;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) dzp[(long)g * H] = ready_value(f32_to_bf16(z[g]));
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) dbacc[g] += v ? z[g] : 0.0f;
+        if (v && s == 0 && a.dc0) a.dc0[(long)b * H + cj] = dc;
+    };
+    auto red_write = [&](const f32x4 (&acc)[NBB]) {
+#pragma unroll
+        for (int i = 0; i < NBB; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[w][4 * (lane >> 4) + v][i * 16 + (lane & 15)] = acc[i][v];
+    };
+    auto red_sum = [&](int r) {
+        float v = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v += red[q][r][cu];
+        return v;
+    };
+
+    if constexpr (MBX > 2) {
+        // Pipelined row blocks: see PipeRows.  Block (s, mb) multiplies dz_s of
+        // its rows into dh_{s-1} and goes on to their gate gradients at step
+        // s - 1, whose inputs were loaded one block ahead.
+        const PipePairs<KCW, PAD> cp{rs_dz, G4, w * KW * 2, lane, 8 * H, pperm, tile, stage[w]};
+        const int nblk = rowend > row0 ? (rowend - row0 + 15) / 16 : 0;
+        const int slow = a.dh0 ? 0 : 1;   // the last step whose dz is multiplied
+        auto trow = [&](int s, int rb0) { return (long)(a.reverse ? a.T - 1 - s : s) * B + rb0; };
+        __shared__ float dcreg[MBX][XT];   // carries of dc, each thread its own element
+        BwdIn<ACT16> in{}, inn{};
+        for (int mb = 0; mb < nblk; ++mb) {
+            const int b = row0 + mb * 16 + cr;
+            float z[4], dc = dc_init(b);
+            load_inputs(a.T - 1, b, in);
+            gate_grads(in, dh_init(b), dc, z);
+            store_dz(a.T - 1, b, z, dc);
+            dcreg[mb][tid] = dc;
+        }
+        if (nblk > 0 && a.T > 1) load_inputs(a.T - 2, row0 + cr, in);
+        if (nblk > 0 && a.T - 1 >= slow) cp.issue(trow(a.T - 1, row0), rowend - row0);
+        wait_own_loads();
+        for (int s = a.T - 1; s >= slow; --s) {
+#pragma unroll 1
+            for (int mb = 0; mb < nblk; ++mb) {
+                const int rb0 = row0 + mb * 16;
+                const bool wrap = mb + 1 >= nblk;
+                const int ns = wrap ? s - 1 : s, nrb0 = wrap ? row0 : rb0 + 16;
+                // the next block: the inputs of its gate gradients, and its rows
+                // as this block's fragments are read
+                if (ns > 0) load_inputs(ns - 1, nrb0 + cr, inn);
+                f32x4 acc[NBB];
+                if (!multiply_and_issue<KCW, NBB, PAD>(cp, trow(s, rb0), rowend - rb0, rf, acc, a.flags, a.timeout,
+                                                       ns >= slow, trow(ns, nrb0), rowend - nrb0))
+                    s_bad = 1;
+                red_write(acc);
+                __syncthreads();
+                if (s_bad) {   // the same decision in every wave
+                    wait_own_loads();
+                    return;
+                }
+                const float dh = red_sum(has_cell ? cr : 0);
+                float z[4], dc = dcreg[mb][tid];
+                if (s > 0) {
+                    gate_grads(in, dh, dc, z);
+                    dcreg[mb][tid] = dc;
+                }
+                // the next block's rows and inputs have landed (before this
+                // block's stores, so that the wait does not cover them)
+                wait_own_loads();
+                asm volatile("" : "+v"(inn.dy), "+v"(inn.g[0]), "+v"(inn.g[1]), "+v"(inn.g[2]), "+v"(inn.g[3]),
+                                  "+v"(inn.c), "+v"(inn.cp));
+                if (s > 0)
+                    store_dz(s - 1, rb0 + cr, z, dc);
+                else if (has_cell && rb0 + cr < rowend)
+                    a.dh0[(long)(rb0 + cr) * H + cj] = f32_to_bf16(dh);
+                in = inn;
+                __syncthreads();   // red is rewritten by the next block
+            }
+        }
+    } else {
+        BwdIn<ACT16> in[MBX];
+        float dhn[MBX], dcn[MBX];
 #pragma unroll
         for (int mb = 0; mb < MBX; ++mb) {
             const int b = row0 + mb * 16 + cr;
-            const bool v = has_cell && b < rowend;
-            if (!ALL_LANES && !v) continue;
-            float gv[4];
-            if constexpr (ACT16) {
-                act_f32(in.g[mb], gv);
-            } else {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) gv[g] = in.g[mb][g];
-            }
-            const float ig = gv[0], fg = gv[1], gg = gv[2], og = gv[3];
-            const float dm = to_f32(in.dy[mb]) + dhn[mb];
-            const float tc = tanh_f(in.c[mb]);
-            const float d_o = dm * tc;
-            const float d_c = dcn[mb] + dm * og * (1.0f - tc * tc);
-            const float d_i = d_c * gg, d_g = d_c * ig, d_f = d_c * in.cp[mb];
-            const float zi = d_i * ig * (1.0f - ig), zf = d_f * fg * (1.0f - fg);
-            const float zg = d_g * (1.0f - gg * gg), zo = d_o * og * (1.0f - og);
-            if (v) {
-                bf16_t *dzp = a.dz + ((long)t * B + b) * G4 + cj;
-                dzp[0] = ready_value(f32_to_bf16(zi));
-                dzp[H] = ready_value(f32_to_bf16(zf));
-                dzp[2 * H] = ready_value(f32_to_bf16(zg));
-                dzp[3 * H] = ready_value(f32_to_bf16(zo));
-            }
-            dbacc[0] += v ? zi : 0.0f;
-            dbacc[1] += v ? zf : 0.0f;
-            dbacc[2] += v ? zg : 0.0f;
-            dbacc[3] += v ? zo : 0.0f;
-            dcn[mb] = d_c * fg;
-            if (v && s == 0 && a.dc0) a.dc0[(long)b * H + cj] = dcn[mb];
+            load_inputs(a.T - 1, b, in[mb]);
+            dhn[mb] = dh_init(b);
+            dcn[mb] = dc_init(b);
         }
-        if (s == 0 && !a.dh0) break;
-        // the next step's inputs travel while this step's dz is exchanged
-        if (s > 0) load_inputs(s - 1, in);
-        // dh_{t-1} for the owned cells: dz_t of this XCD's rows times the resident R^T rows
+        for (int s = a.T - 1; s >= 0; --s) {
+            const int t = a.reverse ? a.T - 1 - s : s;
+            // gate gradients of the owned cells.  Every lane computes them (lanes
+            // without a cell or row loaded zeros) and only the stores depend on
+            // the lane: each prefetched input is then consumed on every path, and
+            // the next prefetch does not wait for the previous one (nor for the
+            // dz stores issued after it) before the exchange copy.
 #pragma unroll
-        for (int mb = 0; mb < MBX; ++mb) {
-            const int rb0 = row0 + mb * 16;
-            if (mb > 0) wait_own_lds();
-            f32x4 acc[NBB];
-#pragma unroll
-            for (int i = 0; i < NBB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (!stage_dz<RB, KCW, NBB, MBX, PAD>(rs_dz, (long)t * B + rb0, G4, w * KW * 2, tile, stage[w], lane,
-                                                  rowend - rb0, rf, acc, a.flags, a.timeout, slot, 8 * H))
-                s_bad = 1;
-#pragma unroll
-            for (int i = 0; i < NBB; ++i)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) red[w][4 * (lane >> 4) + v][i * 16 + (lane & 15)] = acc[i][v];
-            __syncthreads();
-            if (s_bad) return;   // the same decision in every wave
-            const int bc = rb0 + cr;
-            if (has_cell && bc < rowend) {
-                float v = 0.0f;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v += red[q][cr][cu];
-                if (s > 0)
-                    dhn[mb] = v;
-                else
-                    a.dh0[(long)bc * H + cj] = f32_to_bf16(v);
+            for (int mb = 0; mb < MBX; ++mb) {
+                float z[4];
+                gate_grads(in[mb], dhn[mb], dcn[mb], z);
+                store_dz(s, row0 + mb * 16 + cr, z, dcn[mb]);
             }
-            __syncthreads();
+            if (s == 0 && !a.dh0) break;
+            // the next step's inputs travel while this step's dz is exchanged
+            if (s > 0) {
+#pragma unroll
+                for (int mb = 0; mb < MBX; ++mb) load_inputs(s - 1, row0 + mb * 16 + cr, in[mb]);
+            }
+            // dh_{t-1} for the owned cells: dz_t of this XCD's rows times the resident R^T rows
+#pragma unroll
+            for (int mb = 0; mb < MBX; ++mb) {
+                const int rb0 = row0 + mb * 16;
+                if (mb > 0) wait_own_lds();
+                f32x4 acc[NBB];
+                if constexpr (MBX == 2) {
+                    const PipePairs<KCW, PAD> cp{rs_dz, G4, w * KW * 2, lane, 8 * H, pperm, tile, stage[w]};
+                    if (!multiply_halves<KCW, NBB, PAD>(cp, (long)t * B + rb0, rowend - rb0, rf, acc, a.flags,
+                                                        a.timeout))
+                        s_bad = 1;
+                } else {
+                    if (!stage_mma_when_ready<RB, KCW, NBB, false, PAD>(rs_dz, (long)t * B + rb0, G4, w * KW * 2,
+                                                                        tile, stage[w], lane, rowend - rb0, rf, acc,
+                                                                        a.flags, a.timeout, slot, 8 * H))
+                        s_bad = 1;
+                }
+                red_write(acc);
+                __syncthreads();
+                if (s_bad) return;   // the same decision in every wave
+                const int b = rb0 + cr;
+                if (has_cell && b < rowend) {
+                    dhn[mb] = red_sum(cr);
+                    if (s == 0) a.dh0[(long)b * H + cj] = f32_to_bf16(dhn[mb]);
+                }
+                __syncthreads();
+            }
         }
     }
     // bias gradient: sum this workgroup's rows (in row order), one partial per XCD

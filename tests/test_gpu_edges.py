@@ -49,6 +49,26 @@ def test_padded_xcd_widths(T, B, H, reverse, states):
         assert gpu["tiling"][3] == 1001 and gpu["tiling"][7] == 1001, gpu["tiling"]
 
 
+# Pipelined row blocks of the XCD-local kernels (33 to 64 rows per XCD, three
+# or four blocks, the last XCD and the last block ragged), at every width's
+# kernel: (T, B, H, reverse, states)
+XCD_BLOCK_CASES = [
+    (4, 257, 256, False, True),    # 33 rows per XCD: a third block of one row; the last XCD 26 rows
+    (3, 384, 512, True, True),     # three whole blocks
+    (2, 505, 1024, False, False),  # four blocks, the last XCD one row short
+    (1, 300, 256, False, True),    # one step: nothing to exchange but dh0
+    (1, 300, 256, True, False),
+    (3, 390, 360, False, True),    # padded width, four blocks
+]
+
+
+@pytest.mark.parametrize("T,B,H,reverse,states", XCD_BLOCK_CASES)
+def test_pipelined_row_blocks(T, B, H, reverse, states):
+    gpu = run_case(T, B, 40, H, 0, "bf16", reverse, H ** -0.5, states)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert gpu["tiling"][3] in (1000, 1001), gpu["tiling"]
+
+
 # Generic persistent kernels (fp32, LSTMP, bf16 wider than 1024): (T, B, I, H,
 # Hp, dtype, reverse, states).  Between them the planned tilings have 1 and 2
 # row blocks per tile and several tiles per workgroup, weights in LDS and
