@@ -708,15 +708,18 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
         }
         // [dW | dR] = dZ^T [X | H_prev] as one product when the shapes allow
         // (H_prev: y of the previous visited step, h0 for the first one)
+        // with h0 and B not a multiple of 32 its step's stages would straddle
+        // two operands: h0 then enters by a small product of its own
         bool fused = false;
-        if (h->dt == DType::BF16 && (B % 32 == 0 || !h0) && T > 1) {
+        const bool h0_apart = h0 && B % 32 != 0;
+        if (h->dt == DType::BF16 && T > 1) {
             GemmDesc g{};
             g.in = h->dt; g.out_f32 = true; g.a_kmajor = false; g.b_kmajor = false;
             g.M = (int)G4; g.N = I + Hr; g.K = (int)TB;
             g.A = dz; g.lda = G4; g.B = x; g.ldb = h->ldx; g.C = dW; g.ldc = I; g.beta = accumulate;
             g.N1 = I;
             g.B2 = y; g.ldb2 = h->ldy; g.b2_bytes = (long)TB * h->ldy * (long)es;
-            g.B3 = h0; g.ldb3 = Hr; g.b3_bytes = (long)B * Hr * (long)es;
+            g.B3 = h0_apart ? nullptr : h0; g.ldb3 = Hr; g.b3_bytes = (long)B * Hr * (long)es;
             if (!d.reverse) {   // k = t*B + b pairs dz_t with y_{t-1} (t >= 1), h0 (t = 0)
                 g.ylo = B; g.yhi = (int)TB; g.yoff = -B; g.hlo = 0;
             } else {            // dz_t with y_{t+1} (t <= T-2), h0 (t = T-1)
@@ -731,11 +734,21 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
                 g.side.sum_dst = db;
                 g.side.sum_acc = accumulate;
             }
-            if (gemm_dual_ok(g)) {
+            if (gemm_dual_ok(g) && gemm_dual_pays(g)) {
                 TRY_HIP("dW|dR", gemm(g, s, K_GEMM_DWR));
                 fused = true;
             }
         }
+        const char *dz_first = static_cast<const char *>(dz) + (size_t)(d.reverse ? T - 1 : 0) * B * G4 * es;
+        auto dR_h0 = [&](int beta) {   // dR (+)= dz of the first visited step times h0
+            GemmDesc g{};
+            g.in = h->dt; g.out_f32 = true; g.a_kmajor = false; g.b_kmajor = false;
+            g.M = (int)G4; g.N = Hr; g.K = B;
+            g.A = dz_first; g.lda = G4;
+            g.B = h0; g.ldb = Hr; g.C = dR; g.ldc = Hr; g.beta = beta;
+            return gemm(g, s, K_GEMM_DR);
+        };
+        if (fused && h0_apart) TRY_HIP("dR(h0)", dR_h0(1));
         if (!fused) {  // dW = dZ^T X
             GemmDesc g{};
             g.in = h->dt; g.out_f32 = true; g.a_kmajor = false; g.b_kmajor = false;
@@ -765,13 +778,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
                 beta = 1;
             }
             if (h0) {
-                const int tf = d.reverse ? T - 1 : 0;
-                GemmDesc g{};
-                g.in = h->dt; g.out_f32 = true; g.a_kmajor = false; g.b_kmajor = false;
-                g.M = (int)G4; g.N = Hr; g.K = B;
-                g.A = dzc + (size_t)tf * B * G4 * es; g.lda = G4;
-                g.B = h0; g.ldb = Hr; g.C = dR; g.ldc = Hr; g.beta = beta;
-                TRY_HIP("dR(h0)", gemm(g, s, K_GEMM_DR));
+                TRY_HIP("dR(h0)", dR_h0(beta));
                 beta = 1;
             }
             if (!beta) TRY_HIP("dR zero", fill_u32(dR, (size_t)G4 * Hr, 0u, s));

@@ -41,7 +41,7 @@ struct GemmArgs {
     int kchunk;                  // K per split (multiple of the stage depth)
     float *partial;              // split > 1: fp32 partials [split][M][N]
     // second column block (see GemmDesc)
-    int N1;
+    int N1, tiles_n1;            // columns and tile columns of the first block
     const char *B2, *B3;
     long ldb2, ldb3, b2_bytes, b3_bytes;
     int ylo, yhi, yoff, hlo, hlen;
@@ -307,7 +307,10 @@ struct DmaOperand {
         r0 = r0_;
     }
 
-    __device__ __forceinline__ void issue(unsigned dst, int k0, int wave, int lane) const
+    // TAIL: chunks of a K-major stage at or past kend (a multiple of 8) load
+    // zeros: their offset lies past every descriptor's end.
+    template <bool TAIL = false>
+    __device__ __forceinline__ void issue(unsigned dst, int k0, int wave, int lane, int kend = 0) const
     {
 #pragma unroll
         for (int i = 0; i < L::NI; ++i) {
@@ -320,6 +323,7 @@ struct DmaOperand {
                 const int n = r0 + row;
                 const long mrow = ilv ? (long)(n & 3) * ilv + (n >> 2) : (long)n;
                 off = (unsigned)(((mrow * ld + k0) << 1) + c * 16);
+                if (TAIL && c * 8 >= kend - k0) off = 0x80000000u;
             } else {
                 const int k = byte / L::RP, p = (byte % L::RP) >> 4;
                 const int c = L::mslot(k, p);
@@ -434,8 +438,11 @@ constexpr int dl_min_blocks()
     return (NW == 4 && NS * (BM + BN) * KD * 2 <= 80 * 1024) ? 2 : 1;
 }
 
+// TAIL: a k-major operand whose K is no multiple of the stage depth (the chunks
+// past K are masked; a kernel of its own because one compare and select per
+// load made the smallest product, 16 x 4096 x 1024, 0.4 us slower).
 template <typename TO, int BM, int BN, bool AK, bool BKM, int KD, int NS, int NWM, int NWN, bool CB = false,
-          bool GT = false>
+          bool GT = false, bool TAIL = false>
 __global__ __launch_bounds__(64 * NWM * NWN, (dl_min_blocks<BM, BN, KD, NS, NWM * NWN>()))
 void gemm_dl_kernel(GemmArgs g)
 {
@@ -469,18 +476,19 @@ void gemm_dl_kernel(GemmArgs g)
     }
     int tm, tn;
     tile_of(g, tile, tm, tn);
-    const int m0 = tm * BM, n0 = tn * BN;
-    // second column block: its own B operand segments, k range and output
+    // second column block: its own tile columns, B operand segments, k range and output
     constexpr bool DUAL_OK = !AK && !BKM;
-    const bool second = DUAL_OK && g.N1 > 0 && n0 >= g.N1;
+    const bool second = DUAL_OK && g.N1 > 0 && tn >= g.tiles_n1;
+    const int m0 = tm * BM, n0 = second ? g.N1 + (tn - g.tiles_n1) * BN : tn * BN;
+    const int nlim = DUAL_OK && g.N1 > 0 && !second ? g.N1 : g.N;   // columns of the tile's block end here
     int kbeg = blockIdx.y * g.kchunk;
     int kend = min(g.K, kbeg + g.kchunk);
     if (second && !g.B3) {   // no h0 segment: only the B2 range contributes
         kbeg = g.ylo;
         kend = g.yhi;
     }
-    // a last partial stage only when both operands are m-major: its rows past
-    // K lie beyond the operands' buffer bounds and load as zeros
+    // a last partial stage: rows past K of an m-major operand lie beyond its
+    // buffer bounds and load as zeros, chunks past K of a k-major one are masked
     const int nst = (kend - kbeg + KD - 1) / KD;
 
     const int tid = threadIdx.x;
@@ -492,18 +500,23 @@ void gemm_dl_kernel(GemmArgs g)
     DmaOperand<BN, BKM, KD, NW> dh;    // B3 (second block only)
     // (second block without an h0 segment: rows of A past its k range read
     // zero, so a last stage that reaches past it adds nothing)
-    da.init(g.A, g.lda, m0, AK ? (long)g.M * g.lda * 2 : (long)(second && !g.B3 ? g.yhi : g.K) * g.lda * 2);
+    // The bounds end with the last row's last element, not with its stride: a
+    // tile's columns past an m-major operand's width must not be read there.
+    auto extent = [](long rows, long ld, long width) { return ((rows - 1) * ld + width) * 2; };
+    const int krows = second && !g.B3 ? g.yhi : g.K;
+    da.init(g.A, g.lda, m0, AK ? extent(g.M, g.lda, g.K) : extent(krows, g.lda, g.M));
     if (!second) {
-        db.init(g.B, g.ldb, n0, BKM ? (long)g.N * g.ldb * 2 : (long)g.K * g.ldb * 2);
+        db.init(g.B, g.ldb, n0, BKM ? extent(g.N, g.ldb, g.K) : extent(g.K, g.ldb, nlim));
         if (GT) db.ilv = g.cell_h;
     } else {
-        db.init(g.B2, g.ldb2, n0 - g.N1, g.b2_bytes);
-        dh.init(g.B3 ? g.B3 : g.B2, g.ldb3, n0 - g.N1, g.B3 ? g.b3_bytes : 0);
+        const int n2 = g.N - g.N1;
+        db.init(g.B2, g.ldb2, n0 - g.N1, g.b2_bytes - (g.ldb2 - n2) * 2);
+        dh.init(g.B3 ? g.B3 : g.B2, g.ldb3, n0 - g.N1, g.B3 ? g.b3_bytes - (g.ldb3 - n2) * 2 : 0);
     }
     auto issue_b = [&](unsigned dst, int k0) {
         if (!second)
-            db.issue(dst, k0, wave, lane);
-        else if (k0 >= g.hlo && k0 < g.hlo + g.hlen)
+            db.template issue<TAIL>(dst, k0, wave, lane, kend);
+        else if (k0 >= g.hlo && k0 < g.hlo + g.hlen)   // (a second block's operands are m-major)
             dh.issue(dst, k0 - g.hlo, wave, lane);
         else
             db.issue(dst, k0 + g.yoff, wave, lane);
@@ -550,13 +563,14 @@ void gemm_dl_kernel(GemmArgs g)
     }
 
     const unsigned sbase = lds_addr(smem);
+    auto issue_stage = [&](int st) {
+        const unsigned st_base = sbase + (st % NS) * STAGE;
+        da.template issue<TAIL>(st_base, kbeg + st * KD, wave, lane, kend);
+        issue_b(st_base + ABYTES, kbeg + st * KD);
+    };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
-        if (s < nst) {
-            const unsigned st_base = sbase + s * STAGE;
-            da.issue(st_base, kbeg + s * KD, wave, lane);
-            issue_b(st_base + ABYTES, kbeg + s * KD);
-        }
+        if (s < nst) issue_stage(s);
 
     for (int st = 0; st < nst; ++st) {
         // stage st has landed once at most the later stages' loads are outstanding
@@ -565,11 +579,7 @@ void gemm_dl_kernel(GemmArgs g)
         else
             waitcnt_vm<0>();
         asm volatile("s_barrier" ::: "memory");
-        if (st + NS - 1 < nst) {
-            const unsigned st_base = sbase + ((st + NS - 1) % NS) * STAGE;
-            da.issue(st_base, kbeg + (st + NS - 1) * KD, wave, lane);
-            issue_b(st_base + ABYTES, kbeg + (st + NS - 1) * KD);
-        }
+        if (st + NS - 1 < nst) issue_stage(st + NS - 1);
         const char *abase = smem + (st % NS) * STAGE;
         const char *bbase = abase + ABYTES;
         // raised wave priority while the stage's products issue: the
@@ -623,7 +633,7 @@ void gemm_dl_kernel(GemmArgs g)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int row = m0 + wm * WM + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                        cv[j][v] = (row < g.M && col < g.N) ? to_f32(cbase[(long)row * ldc + ccol(col)]) : 0.0f;
+                        cv[j][v] = (row < g.M && col < nlim) ? to_f32(cbase[(long)row * ldc + ccol(col)]) : 0.0f;
                     }
                 }
 #pragma unroll
@@ -703,7 +713,7 @@ void gemm_dl_kernel(GemmArgs g)
                     const int q = r * 64 + lane, rr = q >> 3, c4 = (q & 7) * 4;
                     const f32x4 x4 = *reinterpret_cast<const f32x4 *>(&scr[rr * SP + c4]);
                     const int row = m0 + wm * WM + i * 32 + rr, col = n0 + wn * WN + j * 32 + c4;
-                    if (row < g.M && col < g.N) {
+                    if (row < g.M && col < nlim) {
                         if (split) {
                             store4<float>(part + (long)row * g.N + col, x4);
                         } else {
@@ -726,7 +736,7 @@ void gemm_dl_kernel(GemmArgs g)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
             const int col = n0 + wn * WN + j * 32 + (lane & 31);
-            if (col >= g.N) continue;
+            if (col >= nlim) continue;
             const float bv = (!split && g.bias) ? g.bias[col] : 0.0f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -847,7 +857,7 @@ hipError_t launch_splitk_reduce(const GemmDesc &d, int splits, hipStream_t s)
 }
 
 template <typename TO, int BM, int BN, bool AK, bool BKM, int KD, int NS, int NWM, int NWN, bool CB = false,
-          bool GT = false>
+          bool GT = false, bool TAIL = false>
 hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
 {
     constexpr int LDS = NS * (BM + BN) * KD * 2;
@@ -859,7 +869,8 @@ hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
     g.C = static_cast<char *>(d.C); g.ldc = d.ldc;
     g.bias = d.bias; g.beta = d.beta;
     const int tiles_m = (d.M + BM - 1) / BM;
-    g.tiles_n = (d.N + BN - 1) / BN;
+    g.tiles_n1 = (d.N1 + BN - 1) / BN;
+    g.tiles_n = g.tiles_n1 + (d.N - d.N1 + BN - 1) / BN;
     g.ntiles = tiles_m * g.tiles_n;
     g.per_xcd = (g.ntiles + 7) / 8;
     g.band = band_width(tiles_m, g.tiles_n, g.per_xcd, BM, BN);
@@ -876,7 +887,7 @@ hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
     g.cell_h = GT ? d.cell_h : 0;
     g.cell_prev = d.cell_prev; g.cell_c = d.cell_c; g.cell_cT = d.cell_cT;
     g.cell_m = static_cast<bf16_t *>(d.cell_m); g.cell_ldm = d.cell_ldm;
-    auto kern = gemm_dl_kernel<TO, BM, BN, AK, BKM, KD, NS, NWM, NWN, CB, GT>;
+    auto kern = gemm_dl_kernel<TO, BM, BN, AK, BKM, KD, NS, NWM, NWN, CB, GT, TAIL>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (e != hipSuccess) return e;
@@ -922,7 +933,7 @@ hipError_t launch_gemm(const GemmDesc &d, int splits, hipStream_t s)
     splits = (d.K + g.kchunk - 1) / g.kchunk;
     if (d.partials > 1 && splits != d.partials) return hipErrorInvalidValue;
     g.partial = splits > 1 ? d.splitk_ws : nullptr;
-    g.N1 = 0; g.B2 = g.B3 = nullptr; g.C2 = nullptr;
+    g.N1 = g.tiles_n1 = 0; g.B2 = g.B3 = nullptr; g.C2 = nullptr;
     g.side = d.side;
     auto kern = gemm_kernel<TI, TO, BM, BN, KB, AK, BKM>;
     if (LDS > 64 * 1024) {
@@ -1010,7 +1021,7 @@ Choice choose(const GemmDesc &d, size_t es)
             return c;
         }
     }
-    if (es == 2 && d.M <= 256 && d.K % 64 == 0 && dl_ok(d, 128, 128, 1)) {
+    if (es == 2 && d.M <= 256 && dl_ok(d, 128, 128, 1)) {
         // skinny products (one step of the stepwise recurrence) stream their
         // weight operand once.  Measured on the wide LSTMP layer's per-step
         // shapes (M = 128): accumulating with a k-contiguous weight, 128x64
@@ -1125,15 +1136,19 @@ Choice choose(const GemmDesc &d, size_t es)
     return best;
 }
 
-// The direct-to-LDS kernel needs whole 32-deep K stages and, for an operand
-// whose rows are the contiguous dimension in memory, whole tiles of rows.
+// The direct-to-LDS kernel loads 16-byte chunks: k-major operands need K a
+// multiple of 8, every operand a leading dimension that is one.  Tiles may
+// reach past M and N: of a k-major operand those rows lie past its bounds and
+// read zero, of an m-major one those columns are the next row's first ones;
+// either feeds only outputs that are not stored.
 bool dl_ok(const GemmDesc &d, int BM, int BN, int splits)
 {
     const char *env = std::getenv("LSTM355_GEMM_DL");
     if (env && env[0] == '0') return false;
-    if (d.K % 32 && (d.a_kmajor || d.b_kmajor)) return false;   // a partial last stage needs k as the row index
-    if (!d.a_kmajor && d.M % BM) return false;
-    if (!d.b_kmajor && d.N % BN) return false;
+    (void)BM;
+    (void)BN;
+    if (d.K % 8 && (d.a_kmajor || d.b_kmajor)) return false;
+    if (d.lda % 8 || d.ldb % 8) return false;
     const long ea = d.a_kmajor ? (long)d.M * d.lda : (long)d.K * d.lda;
     const long eb = d.b_kmajor ? (long)d.N * d.ldb : (long)d.K * d.ldb;
     if (ea * 2 > 0x7fffffffL || eb * 2 > 0x7fffffffL) return false;
@@ -1152,13 +1167,25 @@ int fit_splits(const GemmDesc &d, int want)
 template <typename TO, bool AK, bool BKM>
 hipError_t launch_tile(int tile, const GemmDesc &d, int splits, hipStream_t s)
 {
+    if constexpr (AK || BKM) {
+        if (d.K % kTileKD[tile]) {   // a partial last stage (tile_fits: these configurations only)
+            if (tile == 19) {
+                if constexpr (AK && BKM) return launch_gemm_dl<TO, 64, 64, AK, BKM, 64, 4, 2, 2, false, false, true>(d, splits, s);
+            }
+            if (tile == 18) {
+                if constexpr (AK) return launch_gemm_dl<TO, 64, 128, AK, BKM, 64, 3, 2, 2, false, false, true>(d, splits, s);
+            }
+            if (d.beta && splits <= 1) return launch_gemm_dl<TO, 128, 128, AK, BKM, 32, 4, 2, 2, true, false, true>(d, 1, s);
+            return launch_gemm_dl<TO, 128, 128, AK, BKM, 32, 4, 2, 2, false, false, true>(d, splits, s);
+        }
+    }
     if (d.beta && splits <= 1) {   // accumulating into C: the 128x128 configurations with staged C reads
-        if (tile == 16 && d.K % 64 == 0) return launch_gemm_dl<TO, 128, 128, AK, BKM, 64, 4, 2, 2, true>(d, 1, s);
-        if (tile == 5 && d.K % 64 == 0) return launch_gemm_dl<TO, 128, 128, AK, BKM, 64, 2, 2, 2, true>(d, 1, s);
-        if (tile == 3 || tile == 5 || tile == 16) return launch_gemm_dl<TO, 128, 128, AK, BKM, 32, 4, 2, 2, true>(d, 1, s);
+        if (tile == 16) return launch_gemm_dl<TO, 128, 128, AK, BKM, 64, 4, 2, 2, true>(d, 1, s);
+        if (tile == 5) return launch_gemm_dl<TO, 128, 128, AK, BKM, 64, 2, 2, 2, true>(d, 1, s);
+        if (tile == 3) return launch_gemm_dl<TO, 128, 128, AK, BKM, 32, 4, 2, 2, true>(d, 1, s);
         if constexpr (AK && BKM) {
-            if (tile == 19 && d.K % 64 == 0) return launch_gemm_dl<TO, 64, 64, AK, BKM, 64, 4, 2, 2, true>(d, 1, s);
-            if (tile == 20 && d.K % 64 == 0) return launch_gemm_dl<TO, 128, 64, AK, BKM, 64, 3, 2, 2, true>(d, 1, s);
+            if (tile == 19) return launch_gemm_dl<TO, 64, 64, AK, BKM, 64, 4, 2, 2, true>(d, 1, s);
+            if (tile == 20) return launch_gemm_dl<TO, 128, 64, AK, BKM, 64, 3, 2, 2, true>(d, 1, s);
         }
     }
     switch (tile) {
@@ -1196,16 +1223,16 @@ hipError_t launch_tile(int tile, const GemmDesc &d, int splits, hipStream_t s)
     }
 }
 
-// Whether tile configuration `t` can run descriptor `d` (whole k stages,
-// whole tiles along an operand whose rows are contiguous in memory, whole
-// tiles per column block).
+// Whether tile configuration `t` can run descriptor `d` (128 rows per tile
+// along an operand whose rows are contiguous in memory, stages within one
+// segment of a second column block; a partial last stage of a k-major operand
+// on three configurations).
 bool tile_fits(const GemmDesc &d, int t)
 {
     if (t < 0 || t >= NTILES) return false;
     const int kd = kTileKD[t];
-    if (d.K % kd && (d.a_kmajor || d.b_kmajor)) return false;
+    if (d.K % kd && (d.a_kmajor || d.b_kmajor) && t != 3 && t != 18 && t != 19) return false;
     if ((!d.a_kmajor && kTileBM[t] < 128) || (!d.b_kmajor && kTileBN[t] < 128)) return false;
-    if (d.N1 > 0 && (d.N1 % kTileBN[t] || d.N % kTileBN[t] || d.M % kTileBM[t])) return false;
     if (d.N1 > 0 && d.B3 && (d.ylo % kd || d.yhi % kd || d.hlo % kd || d.hlen % kd))
         return false;   // stages stay in one segment
     return dl_ok(d, kTileBM[t], kTileBN[t], 1);
@@ -1231,19 +1258,26 @@ bool env_choice(Choice *c)
     return true;
 }
 
+// Tiles of side x side of a product with a second column block.
+long dual_tiles(const GemmDesc &d, int side)
+{
+    return (long)((d.M + side - 1) / side) * ((d.N1 + side - 1) / side + (d.N - d.N1 + side - 1) / side);
+}
+
 template <typename TI, typename TO, bool AK, bool BKM>
 hipError_t dispatch_tiles(const GemmDesc &d, hipStream_t s)
 {
     if constexpr (sizeof(TI) == 2 && !AK && !BKM) {
         if (d.N1 > 0) {   // two column blocks: no split; 128x128 tiles, 64-deep stages where they fit
             Choice c{5, 1};
-            // 256x256 tiles of 16 waves once the launch's tiles fill the CUs at
-            // least once (BigLSTM's 32768 x 2048 product: 368 -> 324 us; the
-            // layer wavefront's four 4096 x 2048 products in one launch: 73.7 ->
-            // 69.8 us at B = 16, 123.9 -> 109.7 us at B = 32; one 4096-row
-            // product's 128 tiles leave half the CUs idle)
+            // 256x256 tiles of 16 waves once the launch's tiles occupy three
+            // quarters of the CUs (BigLSTM's 32768 x 2048 product: 368 -> 324 us;
+            // the layer wavefront's four 4096 x 2048 products in one launch: 73.7
+            // -> 69.8 us at B = 16, 123.9 -> 109.7 us at B = 32; 192 tiles, 4096 x
+            // 3072 x 12800: 376 -> 325 us; one 4096 x 2048 product's 128 tiles
+            // leave half the CUs idle)
             const long nb = d.nbatch > 1 ? d.nbatch : 1;
-            if ((long)(d.M / 256) * (d.N / 256) * nb >= 256 && tile_fits(d, 22)) c.tile = 22;
+            if (dual_tiles(d, 256) * nb >= 192 && tile_fits(d, 22)) c.tile = 22;
             env_choice(&c);
             if (!tile_fits(d, c.tile)) c.tile = 5;
             if (!tile_fits(d, c.tile)) c.tile = 3;
@@ -1289,7 +1323,7 @@ hipError_t dispatch_layout(const GemmDesc &d, hipStream_t s)
 bool gemm_dual_ok(const GemmDesc &d)
 {
     if (d.in != DType::BF16 || d.a_kmajor || d.b_kmajor || !d.out_f32) return false;
-    if (d.N1 <= 0 || d.N1 >= d.N || d.N1 % 128 || d.N % 128 || d.M % 128) return false;
+    if (d.N1 <= 0 || d.N1 >= d.N || d.N1 % 8 || d.N % 8 || d.ldb2 % 8 || (d.B3 && d.ldb3 % 8)) return false;
     if (d.ylo < 0 || d.yhi > d.K || d.ylo >= d.yhi) return false;
     // with an h0 segment, stages of 32 k must not straddle a segment boundary;
     // without one, the second block runs over [ylo, yhi) alone
@@ -1297,6 +1331,14 @@ bool gemm_dual_ok(const GemmDesc &d)
     if (d.B3 && (d.hlo < 0 || d.hlo + d.hlen > d.K)) return false;
     return dl_ok(d, 128, 128, 1);
 }
+
+// One product saves the other's launch, its reads of A and both split-K
+// reductions, but is not split: with fewer 128x128 tiles than CUs each tile's
+// whole K is one workgroup's work.  Measured, one product against two split:
+// H = I = 256 K = 1600 22 / 32 us, 6400 67 / 58, 25600 251 / 173; H = I = 512
+// (128 tiles) K = 1600 24 / 45, 6400 71 / 70, 25600 311 / 195; H = I = 1024
+// (512 tiles) K = 6400 110 / 153.
+bool gemm_dual_pays(const GemmDesc &d) { return dual_tiles(d, 128) >= 256 || d.K <= 4096; }
 
 // fp16 C only where the product takes the 256x256 tile unsplit (the same
 // shapes on which choose() picks it: more than 1024 rows, at least 192 tiles).

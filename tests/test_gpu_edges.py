@@ -96,3 +96,22 @@ GENERIC_CASES = [
 def test_generic_kernels(T, B, I, H, Hp, dtype, reverse, states):
     gpu = run_case(T, B, I, H, Hp, dtype, reverse, min(0.3, H ** -0.5), states)
     assert gpu["tiling"][3] not in (1000, 1001, 2000), gpu["tiling"]
+
+
+# Time-parallel products off their tiles: widths that are no multiple of a
+# tile or of a k stage, T*B no multiple of one, h0 of a batch that is no
+# multiple of 32 (its own product), outputs in the halves of wider rows:
+# (T, B, I, H, Hp, reverse, states)
+GEMM_CASES = [
+    (9, 13, 8, 40, 0, False, True),        # one partial stage each
+    (5, 33, 136, 264, 0, True, True),      # k = 136: two stages and a chunk
+    (17, 67, 328, 520, 0, False, False),   # more than 1024 rows, three ragged tiles per block
+    (6, 250, 1096, 648, 0, False, True),   # both blocks end inside a 256-wide tile
+    (4, 40, 72, 1000, 0, True, False),
+    (5, 100, 200, 328, 72, False, True),   # LSTMP: Hp and 4H off the tiles
+]
+
+
+@pytest.mark.parametrize("T,B,I,H,Hp,reverse,states", GEMM_CASES)
+def test_ragged_products(T, B, I, H, Hp, reverse, states):
+    run_case(T, B, I, H, Hp, "bf16", reverse, max(I, H) ** -0.5, states)
