@@ -756,6 +756,162 @@ void gemm_dl_kernel(GemmArgs g)
     run_side_job(g.side, (long)blockIdx.y * gridDim.x + blockIdx.x, (long)gridDim.x * gridDim.y);
 }
 
+// ---------------------------------------------------------------------------
+// fp32 kernel: 64x64 tiles of C, four waves of one 32x32 block each, operands
+// staged by direct global -> LDS loads in a ring of F32_NS stages of 32 k
+// (8 KiB per operand and stage).
+//
+// The fp32 matrix instructions (256 FLOP per cycle and CU) bound these products,
+// so the tile is small: five workgroups per CU (two stages of 16 KiB each; with
+// three or four stages fewer fit, 5-10 % slower) hide each other's stage waits
+// and epilogues, and a 64x64 tile still needs only 16 bytes of operands per
+// cycle.  Against 128x128 tiles staged through registers: 1600 x 4096 x 1024
+// (k-major) 157 -> 128 us (105 TFLOP/s of 153 a large library product reaches),
+// 1600 x 1024 x 4096 207 -> 144 us, 4096 x 1024 x 1600 (m-major) 185 -> 111 us,
+// the tiny layer's 32 x 32 x 256 27 -> 9 us.  LDS rows are swizzled in 16-byte chunks:
+//   K-major tile [64 rows][128 bytes]: as the bf16 kernel's 64-deep stages;
+//   M-major tile [32 k][256 bytes]: chunk c of row k lives at slot
+//     c ^ (8 * ((k / 4) & 1)): the two halves of a wave read rows 4 apart, and
+//     then find them in different banks.
+// A K-major fragment is one 16-byte read per lane (4 k), an M-major one four
+// 4-byte reads; either way lane group q of substep s holds k = 8s + 4q + e.
+// ---------------------------------------------------------------------------
+constexpr int F32_T = 64, F32_KD = 32, F32_NS = 2;
+constexpr int F32_OPER = F32_T * F32_KD * 4, F32_STAGE = 2 * F32_OPER;
+
+template <bool KMAJ>
+struct F32Operand {
+    using LK = DlLayout<F32_T, true, 64, 4>;   // 128-byte rows
+    u32x4 rsrc;
+    unsigned off[2];      // byte offsets of this lane's two chunks of the next stage
+    int kc[2];            // K-major: first k of each chunk within a stage
+    unsigned step;
+
+    __device__ __forceinline__ void init(const char *base, long ld, int r0, long extent, int kbeg, int wave, int lane)
+    {
+        rsrc = buffer_desc(base, extent * 4);
+        step = (unsigned)(KMAJ ? F32_KD * 4 : F32_KD * ld * 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int byte = (wave * 2 + i) * 1024 + lane * 16;
+            if (KMAJ) {
+                const int row = byte >> 7, c = LK::kslot(row, (byte & 127) >> 4);
+                kc[i] = c * 4;
+                off[i] = (unsigned)((((long)(r0 + row) * ld + kbeg) + c * 4) * 4);
+            } else {
+                const int k = byte >> 8, c = ((byte & 255) >> 4) ^ (8 * ((k >> 2) & 1));
+                kc[i] = 0;
+                off[i] = (unsigned)((((long)(kbeg + k) * ld + r0) + c * 4) * 4);
+            }
+        }
+    }
+    // left: k from the stage's first to the end of the split's range
+    __device__ __forceinline__ void issue(unsigned dst, int wave, int left)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const unsigned o = KMAJ && kc[i] >= left ? 0x80000000u : off[i];
+            dma16(rsrc, __builtin_amdgcn_readfirstlane(dst + (wave * 2 + i) * 1024), o);
+            off[i] += step;
+        }
+    }
+    __device__ static __forceinline__ u32x4 frag(const char *tile, int rowbase, int s, int lane)
+    {
+        const int m = rowbase + (lane & 31), q = lane >> 5;
+        if (KMAJ) return *reinterpret_cast<const u32x4 *>(tile + m * 128 + LK::kslot(m, 2 * s + q) * 16);
+        u32x4 f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 8 * s + 4 * q + e;
+            f[e] = *reinterpret_cast<const unsigned *>(tile + k * 256 + (((m >> 2) ^ (8 * q)) << 4) + (m & 3) * 4);
+        }
+        return f;
+    }
+};
+
+template <bool AK, bool BKM>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g)
+{
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int bid = blockIdx.x;
+    const int tile = (bid & 7) * g.per_xcd + (bid >> 3);
+    if (tile >= g.ntiles) {
+        run_side_job(g.side, (long)blockIdx.y * gridDim.x + blockIdx.x, (long)gridDim.x * gridDim.y);
+        return;
+    }
+    int tm, tn;
+    tile_of(g, tile, tm, tn);
+    const int m0 = tm * F32_T, n0 = tn * F32_T;
+    const int kbeg = blockIdx.y * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+    const int nst = (kend - kbeg + F32_KD - 1) / F32_KD;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave & 1, wn = wave >> 1;
+
+    // bounds end with the last row's last element (see the bf16 kernel)
+    auto extent = [](long rows, long ld, long width) { return (rows - 1) * ld + width; };
+    F32Operand<AK> da;
+    F32Operand<BKM> db;
+    da.init(g.A, g.lda, m0, AK ? extent(g.M, g.lda, g.K) : extent(kend, g.lda, g.M), kbeg, wave, lane);
+    db.init(g.B, g.ldb, n0, BKM ? extent(g.N, g.ldb, g.K) : extent(kend, g.ldb, g.N), kbeg, wave, lane);
+
+    // two sums, of every other 8 k: half the length of each fp32 sum, and no
+    // product waits for the one before
+    f32x16 acc, acc1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = acc1[v] = 0.0f;
+    const unsigned sbase = lds_addr(smem);
+    auto issue = [&](int st) {
+        const unsigned dst = sbase + (st % F32_NS) * F32_STAGE;
+        da.issue(dst, wave, kend - kbeg - st * F32_KD);
+        db.issue(dst + F32_OPER, wave, kend - kbeg - st * F32_KD);
+    };
+    constexpr int LPW = 4;   // loads per wave and stage
+#pragma unroll
+    for (int st = 0; st < F32_NS - 1; ++st)
+        if (st < nst) issue(st);
+    for (int st = 0; st < nst; ++st) {
+        if (st + F32_NS - 2 < nst)
+            waitcnt_vm<(F32_NS - 2) * LPW>();
+        else
+            waitcnt_vm<0>();
+        asm volatile("s_barrier" ::: "memory");
+        if (st + F32_NS - 1 < nst) issue(st + F32_NS - 1);
+        const char *ta = smem + (st % F32_NS) * F32_STAGE, *tb = ta + F32_OPER;
+#pragma unroll
+        for (int s = 0; s < F32_KD / 8; ++s)
+            mfma32(s & 1 ? acc1 : acc, F32Operand<AK>::frag(ta, wm * 32, s, lane),
+                   F32Operand<BKM>::frag(tb, wn * 32, s, lane), float{});
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] += acc1[v];
+
+    // lane holds rows 8 (v / 4) + 4 (lane / 32) + v % 4 of column lane % 32
+    const int col = n0 + wn * 32 + (lane & 31);
+    const int rbase = m0 + wm * 32 + 4 * (lane >> 5);
+    if (col < g.N) {
+        const bool split = g.partial != nullptr;
+        float *cp = split ? g.partial + (long)blockIdx.y * g.M * g.N : reinterpret_cast<float *>(g.C);
+        const long ld = split ? g.N : g.ldc;
+        const float bv = (!split && g.bias) ? g.bias[col] : 0.0f;
+        if (!split && g.beta) {   // all of C's values are read before the first store
+            float cv[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = rbase + 8 * (v >> 2) + (v & 3);
+                cv[v] = row < g.M ? cp[(long)row * ld + col] : 0.0f;
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] += cv[v];
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = rbase + 8 * (v >> 2) + (v & 3);
+            if (row < g.M) cp[(long)row * ld + col] = acc[v] + bv;
+        }
+    }
+    run_side_job(g.side, (long)blockIdx.y * gridDim.x + blockIdx.x, (long)gridDim.x * gridDim.y);
+}
+
 // C[m][n] = (beta ? C : 0) + bias[n] + sum over splits of partial[s][m][n], in split order.
 template <typename TO>
 __global__ __launch_bounds__(256) void splitk_reduce(const float *__restrict__ partial, int splits, int M, int N,
@@ -945,6 +1101,67 @@ hipError_t launch_gemm(const GemmDesc &d, int splits, hipStream_t s)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1 || d.partials > 1) return e;
     return launch_splitk_reduce<TO>(d, splits, s);
+}
+
+// The fp32 kernel addresses operands with 32-bit byte offsets, in 16-byte chunks.
+bool f32_ok(const GemmDesc &d)
+{
+    if (d.K % 4 && (d.a_kmajor || d.b_kmajor)) return false;
+    if (d.lda % 4 || d.ldb % 4 || d.nbatch > 1 || d.N1 > 0 || d.partials > 1) return false;
+    const long ea = d.a_kmajor ? (long)d.M * d.lda : (long)d.K * d.lda;
+    const long eb = d.b_kmajor ? (long)d.N * d.ldb : (long)d.K * d.ldb;
+    // offsets run up to two stages and a tile past the end
+    const long slack = 3L * F32_KD * (d.lda > d.ldb ? d.lda : d.ldb) + 64L * (d.lda > d.ldb ? d.lda : d.ldb);
+    return (ea + slack) * 4 <= 0x7fffffffL && (eb + slack) * 4 <= 0x7fffffffL;
+}
+
+// Splits along K so that the 64x64 tiles fill the CUs in whole rounds: a CU's
+// matrix cores take 32 cycles per tile and k, a split adds the partials'
+// traffic and the reduction's launch.
+int f32_splits(const GemmDesc &d)
+{
+    const long tiles = (long)((d.M + F32_T - 1) / F32_T) * ((d.N + F32_T - 1) / F32_T);
+    int best = 1;
+    double best_t = 1e30;
+    for (int sp = 1; sp <= 32; sp *= 2) {
+        if (sp > 1 && (!d.splitk_ws || (size_t)sp * d.M * d.N > d.splitk_ws_floats || d.K / sp < 2 * F32_KD)) break;
+        const double rounds = (double)((tiles * sp + 255) / 256);
+        double t = rounds * ((double)d.K / sp * 32.0 / 2.2e9 + 0.5e-6);
+        // a lone workgroup on a CU pays its stages' latency, about 0.35 us each
+        const double lone = (double)d.K / sp / F32_KD * 0.35e-6;
+        if (lone > t) t = lone;
+        if (sp > 1) t += ((double)sp + 1.0) * d.M * d.N * 4.0 / 4.0e12 + 5e-6;
+        if (t < best_t * 0.97) {
+            best_t = t;
+            best = sp;
+        }
+    }
+    return best;
+}
+
+template <bool AK, bool BKM>
+hipError_t launch_gemm_f32(const GemmDesc &d, hipStream_t s)
+{
+    GemmArgs g{};
+    int splits = f32_splits(d);
+    g.M = d.M; g.N = d.N; g.K = d.K;
+    g.A = static_cast<const char *>(d.A); g.lda = d.lda;
+    g.B = static_cast<const char *>(d.B); g.ldb = d.ldb;
+    g.C = static_cast<char *>(d.C); g.ldc = d.ldc;
+    g.bias = d.bias; g.beta = d.beta;
+    const int tiles_m = (d.M + F32_T - 1) / F32_T;
+    g.tiles_n = (d.N + F32_T - 1) / F32_T;
+    g.ntiles = tiles_m * g.tiles_n;
+    g.per_xcd = (g.ntiles + 7) / 8;
+    g.band = band_width(tiles_m, g.tiles_n, g.per_xcd, F32_T, F32_T);
+    g.kchunk = ((d.K + splits - 1) / splits + F32_KD - 1) / F32_KD * F32_KD;
+    splits = (d.K + g.kchunk - 1) / g.kchunk;
+    g.partial = splits > 1 ? d.splitk_ws : nullptr;
+    g.side = d.side;
+    hipLaunchKernelGGL((gemm_f32_kernel<AK, BKM>), dim3(g.per_xcd * 8, splits), dim3(256), F32_NS * F32_STAGE, s, g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || splits == 1) return e;
+    return launch_splitk_reduce<float>(d, splits, s);
 }
 
 // Tile and split choice: a crude model of per-CU efficiency per tile shape,
@@ -1286,6 +1503,9 @@ hipError_t dispatch_tiles(const GemmDesc &d, hipStream_t s)
         }
     }
     if (d.N1 > 0) return hipErrorInvalidValue;
+    if constexpr (sizeof(TI) == 4) {
+        if (f32_ok(d)) return launch_gemm_f32<AK, BKM>(d, s);
+    }
     Choice c = choose(d, sizeof(TI));
     if (d.partials > 1) {   // exactly the requested parts, all of them in the workspace
         if (d.nbatch > 1 || fit_splits(d, d.partials) != d.partials) return hipErrorInvalidValue;

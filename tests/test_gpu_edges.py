@@ -115,3 +115,17 @@ GEMM_CASES = [
 @pytest.mark.parametrize("T,B,I,H,Hp,reverse,states", GEMM_CASES)
 def test_ragged_products(T, B, I, H, Hp, reverse, states):
     run_case(T, B, I, H, Hp, "bf16", reverse, max(I, H) ** -0.5, states)
+
+
+# The fp32 products: (T, B, I, H, reverse, states)
+F32_CASES = [
+    (3, 5, 8, 16, False, True),       # smaller than a tile and than a stage
+    (9, 7, 40, 72, True, True),       # one tile and a bit on every side
+    (40, 33, 264, 136, False, False), # several tiles, split along a long k
+    (7, 19, 1000, 200, False, True),
+]
+
+
+@pytest.mark.parametrize("T,B,I,H,reverse,states", F32_CASES)
+def test_fp32_products(T, B, I, H, reverse, states):
+    run_case(T, B, I, H, 0, "f32", reverse, max(I, H) ** -0.5, states)
