@@ -39,6 +39,7 @@ struct GemmArgs {
     int tiles_n, ntiles, per_xcd;
     int band;                    // tile columns per band of the tile order (tiles_n: row-major)
     int kchunk;                  // K per split (multiple of the stage depth)
+    int split_major;             // order of (tile, split) pairs over the XCDs
     float *partial;              // split > 1: fp32 partials [split][M][N]
     // second column block (see GemmDesc)
     int N1, tiles_n1;            // columns and tile columns of the first block
@@ -468,9 +469,24 @@ void gemm_dl_kernel(GemmArgs g)
     constexpr int LPW = LA::NI + LB::NI;          // DMA instructions per wave per stage
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-    const int bid = blockIdx.x;
-    const int tile = (bid & 7) * g.per_xcd + (bid >> 3);
-    if (tile >= g.ntiles) {
+    // Workgroup -> (tile, split).  Consecutive workgroups go to the XCDs in
+    // turn, so each XCD takes a contiguous share of the tiles (and every split
+    // of them) or, split_major, of the splits (and every tile of them): few
+    // tiles split many ways then read each k range of both operands on one XCD.
+    int tile, split_id = blockIdx.y;
+    bool idle;
+    if (g.split_major) {
+        const int lin = blockIdx.y * gridDim.x + blockIdx.x;
+        const int total = g.ntiles * gridDim.y, per = (total + 7) >> 3;
+        const int id = (lin & 7) * per + (lin >> 3);
+        idle = (lin >> 3) >= per || id >= total;
+        split_id = id / g.ntiles;
+        tile = id - split_id * g.ntiles;
+    } else {
+        tile = (blockIdx.x & 7) * g.per_xcd + (blockIdx.x >> 3);
+        idle = tile >= g.ntiles;
+    }
+    if (idle) {
         run_side_job(g.side, (long)blockIdx.y * gridDim.x + blockIdx.x, (long)gridDim.x * gridDim.y);
         return;
     }
@@ -481,7 +497,7 @@ void gemm_dl_kernel(GemmArgs g)
     const bool second = DUAL_OK && g.N1 > 0 && tn >= g.tiles_n1;
     const int m0 = tm * BM, n0 = second ? g.N1 + (tn - g.tiles_n1) * BN : tn * BN;
     const int nlim = DUAL_OK && g.N1 > 0 && !second ? g.N1 : g.N;   // columns of the tile's block end here
-    int kbeg = blockIdx.y * g.kchunk;
+    int kbeg = split_id * g.kchunk;
     int kend = min(g.K, kbeg + g.kchunk);
     if (second && !g.B3) {   // no h0 segment: only the B2 range contributes
         kbeg = g.ylo;
@@ -601,7 +617,7 @@ void gemm_dl_kernel(GemmArgs g)
     }
 
     const bool split = g.partial != nullptr;
-    float *part = split ? g.partial + (long)blockIdx.y * g.M * g.N : nullptr;
+    float *part = split ? g.partial + (long)split_id * g.M * g.N : nullptr;
     TO *cbase = reinterpret_cast<TO *>(second ? g.C2 : g.C);
     const long ldc = second ? g.ldc2 : g.ldc;
     const int coff = second ? g.N1 : 0;
@@ -1033,6 +1049,11 @@ hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
     g.kchunk = ((d.K + splits - 1) / splits + KD - 1) / KD * KD;
     splits = (d.K + g.kchunk - 1) / g.kchunk;
     if (d.partials > 1 && splits != d.partials) return hipErrorInvalidValue;
+    // from eight splits on an XCD has whole splits to itself.  The LSTMP carry
+    // 128 x 1024 x 32768 split 32 ways 25 -> 20 us, BigLSTM's step 2560 -> 2442
+    // us; at H = 4096, Hp = 512, 64 rows 1356 -> 1219 us; from two splits on
+    // BigLSTM took 2486 us
+    g.split_major = splits >= 8;
     g.partial = splits > 1 ? d.splitk_ws : nullptr;
     g.N1 = d.N1;
     g.B2 = static_cast<const char *>(d.B2); g.ldb2 = d.ldb2; g.b2_bytes = d.b2_bytes;

@@ -279,11 +279,9 @@ struct PipeRows {
 
 // 16 rows in chunk pairs (pair_voff, pair_frag).  LDS block p holds pair
 // p ^ pperm of the slice (and the caller's weights are loaded in that order).
-// Rows of dz lie 8 KiB apart at H = 1024, a multiple of the L2's channel
-// interleave: one pair of all rows and waves falls in 4 of the 16 channels, so
-// the workgroups of an XCD, which copy the same rows at the same time, take
-// their pairs in different orders (pperm from the slot; B = 512 backward 662 ->
-// 611 us per layer, B = 256 305 -> 297 us).
+// The workgroups of an XCD copy the same rows at the same time; taking their
+// pairs in different orders (pperm from the slot) they ask the L2 for different
+// lines (B = 512 backward 662 -> 611 us per layer, B = 256 305 -> 297 us).
 template <int KCW, bool PAD>
 struct PipePairs {
     u32x4 rs;
