@@ -473,9 +473,12 @@ void gemm_dl_kernel(GemmArgs g)
     // turn, so each XCD takes a contiguous share of the tiles (and every split
     // of them) or, split_major, of the splits (and every tile of them): few
     // tiles split many ways then read each k range of both operands on one XCD.
+    // (Only in the configuration that the long-K skinny products take, so that
+    // the smallest products do not pay for the test.)
+    constexpr bool SPLIT_MAJOR = BM == 128 && BN == 128 && KD == 64 && NS == 4;
     int tile, split_id = blockIdx.y;
     bool idle;
-    if (g.split_major) {
+    if (SPLIT_MAJOR && g.split_major) {
         const int lin = blockIdx.y * gridDim.x + blockIdx.x;
         const int total = g.ntiles * gridDim.y, per = (total + 7) >> 3;
         const int id = (lin & 7) * per + (lin >> 3);
@@ -1050,8 +1053,8 @@ hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
     splits = (d.K + g.kchunk - 1) / g.kchunk;
     if (d.partials > 1 && splits != d.partials) return hipErrorInvalidValue;
     // from eight splits on an XCD has whole splits to itself.  The LSTMP carry
-    // 128 x 1024 x 32768 split 32 ways 25 -> 20 us, BigLSTM's step 2560 -> 2442
-    // us; at H = 4096, Hp = 512, 64 rows 1356 -> 1219 us; from two splits on
+    // 128 x 1024 x 32768 split 32 ways 25 -> 20 us, BigLSTM's step 2560 -> 2454
+    // us; at H = 4096, Hp = 512, 64 rows 1356 -> 1228 us; from two splits on
     // BigLSTM took 2486 us
     g.split_major = splits >= 8;
     g.partial = splits > 1 ? d.splitk_ws : nullptr;
