@@ -55,7 +55,7 @@ typedef enum {
     LSTM_ERR_UNSUPPORTED = 2,  /* shape has no kernel configuration on this device */
     LSTM_ERR_WORKSPACE = 3,    /* a reserve or workspace shorter than the call needs */
     LSTM_ERR_HIP = 4,          /* a HIP runtime call or kernel launch failed */
-    LSTM_ERR_TIMEOUT = 5       /* a grid barrier's watchdog expired (see lstm_check) */
+    LSTM_ERR_TIMEOUT = 5       /* a watchdog of a kernel's wait expired (see lstm_check) */
 } lstm_status_t;
 
 typedef enum {
@@ -88,7 +88,7 @@ lstm_status_t lstm_create(const lstm_desc_t *desc, lstm_handle_t *out);
  * handle and device. */
 size_t lstm_reserve_size(lstm_handle_t h);
 
-/* Bytes of `workspace` (scratch for one call at a time: barrier counters,
+/* Bytes of `workspace` (scratch for one call at a time: flags,
  * the gate gradients dz[T][B][4H], transposed weight copies). */
 size_t lstm_workspace_size(lstm_handle_t h);
 
@@ -219,10 +219,11 @@ size_t lstm_backward_stack_workspace_size(int L, const lstm_handle_t *h);
  * launch but relies on the device not running other kernels beside them;
  * if it does, their waits time out and lstm_check reports LSTM_ERR_TIMEOUT.
  * Use the cooperative launch when other streams (for example collectives
- * overlapping the backward pass) share the device. */
+ * overlapping the backward pass) share the device.  Widths other than 256,
+ * 512 and 1024, fp32 and LSTMP layers always launch cooperatively. */
 
 /* Synchronises `stream` and reports whether any kernel of the library gave up
- * at a grid barrier on the current device since the last check
+ * waiting on the current device since the last check
  * (LSTM_ERR_TIMEOUT; the device-wide flag is then cleared).  Outputs of such a
  * call are undefined.  `workspace` (the one the checked calls used) may be
  * NULL, as after lstm_forward_noalloc: the flags are kept per device. */

@@ -1788,7 +1788,10 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
 // lstm_check reports it.  When other kernels may occupy CUs at the same time
 // (another stream, collectives overlapping the backward pass),
 // LSTM355_XCD_LAUNCH=cooperative selects a cooperative launch, which waits
-// until all 256 workgroups can be resident.
+// until all 256 workgroups can be resident.  The padded widths always launch
+// cooperatively (COOP), as the generic kernels do: layers of these widths may
+// run on several streams at once, and as plain dispatches two of them could
+// each hold CUs that the other one's consumers wait for.
 constexpr int ONE_PER_CU_LDS = 96 * 1024;   // more than half of a CU's 160 KiB
 
 bool cooperative_requested()
@@ -1797,7 +1800,7 @@ bool cooperative_requested()
     return env && std::strcmp(env, "cooperative") == 0;
 }
 
-template <auto kernel>
+template <auto kernel, bool COOP = false>
 hipError_t launch256(hipStream_t s, void *argp)
 {
     struct Cfg {
@@ -1817,7 +1820,7 @@ hipError_t launch256(hipStream_t s, void *argp)
     if (cfg.per_cu != 1) return hipErrorCooperativeLaunchTooLarge;
     void *args[] = {argp};
     const void *f = reinterpret_cast<const void *>(kernel);
-    if (cooperative_requested())
+    if (COOP || cooperative_requested())
         return hipLaunchCooperativeKernel(f, dim3(NXCD * WG_PER_XCD), dim3(XT), args, cfg.dyn, s);
     return hipLaunchKernel(f, dim3(NXCD * WG_PER_XCD), dim3(XT), args, cfg.dyn, s);
 }
@@ -2105,7 +2108,7 @@ hipError_t launch_forward_xcd(const RecShape &sh, const FwdBufs &bf, unsigned lo
     FWD_CASE(16, 1) FWD_CASE(16, 2) FWD_CASE(16, 4)
     FWD_CASE(32, 1) FWD_CASE(32, 2) FWD_CASE(32, 4)
 #define FWD_CASE_PAD(HN_, M_) \
-    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_fwd_xcd<HN_, M_, false, false, true>>(s, &a);
+    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_fwd_xcd<HN_, M_, false, false, true>, true>(s, &a);
     if (a.gx) return hipErrorInvalidValue;   // the other widths keep an fp32 projection
     FWD_CASE_PAD(8, 1) FWD_CASE_PAD(8, 2) FWD_CASE_PAD(8, 4)
     FWD_CASE_PAD(16, 1) FWD_CASE_PAD(16, 2) FWD_CASE_PAD(16, 4)
@@ -2159,7 +2162,7 @@ hipError_t launch_backward_xcd(const RecShape &sh, const BwdBufs &bf, unsigned l
     BWD_CASE(16, 1) BWD_CASE(16, 2) BWD_CASE(16, 4)
     BWD_CASE(32, 1) BWD_CASE(32, 2) BWD_CASE(32, 4)
 #define BWD_CASE_PAD(HN_, M_) \
-    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_bwd_xcd<HN_, M_, false, true>>(s, &a);
+    if (sh.H <= 32 * HN_ && m == M_) return launch256<lstm_bwd_xcd<HN_, M_, false, true>, true>(s, &a);
     BWD_CASE_PAD(8, 1) BWD_CASE_PAD(8, 2) BWD_CASE_PAD(8, 4)
     BWD_CASE_PAD(16, 1) BWD_CASE_PAD(16, 2) BWD_CASE_PAD(16, 4)
     BWD_CASE_PAD(32, 1) BWD_CASE_PAD(32, 2) BWD_CASE_PAD(32, 4)

@@ -129,3 +129,53 @@ F32_CASES = [
 @pytest.mark.parametrize("T,B,I,H,reverse,states", F32_CASES)
 def test_fp32_products(T, B, I, H, reverse, states):
     run_case(T, B, I, H, 0, "f32", reverse, max(I, H) ** -0.5, states)
+
+
+@pytest.mark.parametrize("B,H,dtype", [(50, 648, "bf16"), (9, 264, "bf16"), (20, 200, "f32")])
+def test_two_streams(B, H, dtype):
+    """Layers of widths without a kernel of their own, in flight on two
+    streams at once: every pass bitwise equal to the layer's pass alone, and
+    no wait of a kernel timed out."""
+    from paper_1907_13257_amd import Layer
+    announce(f"two streams B{B} H{H} {dtype}")
+    T, I = 12, 64
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+
+    def uniform(*shape, dtype=td):
+        return ((torch.rand(shape, generator=g, device="cuda") * 2 - 1) * H ** -0.5).to(dtype)
+
+    sets = []
+    for _ in range(2):
+        p = dict(W=uniform(4 * H, I), R=uniform(4 * H, H), b=uniform(4 * H, dtype=torch.float32))
+        sets.append(dict(p=p, layer=Layer(T, B, I, H, 0, dtype), x=uniform(T, B, I), dy=uniform(T, B, H),
+                         y=torch.empty((T, B, H), dtype=td, device="cuda"),
+                         hT=torch.empty((B, H), dtype=td, device="cuda"),
+                         cT=torch.empty((B, H), dtype=torch.float32, device="cuda"),
+                         dx=torch.empty((T, B, I), dtype=td, device="cuda"),
+                         grads={"d" + k: torch.empty(v.shape, dtype=torch.float32, device="cuda")
+                                for k, v in p.items()}))
+
+    def step(s):
+        p = s["p"]
+        s["layer"].forward(s["x"], p["W"], p["R"], p["b"], y=s["y"], hT=s["hT"], cT=s["cT"])
+        s["layer"].backward(s["dy"], s["x"], p["W"], p["R"], s["y"], s["grads"], dx=s["dx"])
+
+    want = []
+    for s in sets:
+        step(s)
+        torch.cuda.synchronize()
+        want.append([v.clone() for v in (s["y"], s["dx"], *s["grads"].values())])
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for st in streams:
+        st.wait_stream(torch.cuda.current_stream())
+    for _ in range(4):
+        for s, st in zip(sets, streams):
+            with torch.cuda.stream(st):
+                step(s)
+    torch.cuda.synchronize()
+    for s, w in zip(sets, want):
+        assert s["layer"].check() == 0
+        for got, ref in zip((s["y"], s["dx"], *s["grads"].values()), w):
+            assert torch.equal(got, ref)
