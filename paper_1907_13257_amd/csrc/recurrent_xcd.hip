@@ -480,6 +480,10 @@ __device__ __forceinline__ bool multiply_and_issue(const PipePairs<KCW, PAD> &cp
     u32x4 fa[2][G];
 #pragma unroll
     for (int g = 0; g < G; ++g) fa[0][g] = cp.frag(g);
+    // the first group's reads are issued before the second's: the counted wait
+    // below relies on it (from then on it orders the groups itself)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c0 = 0; c0 < KCW; c0 += G) {
         u32x4 (&cur)[G] = fa[(c0 / G) & 1];

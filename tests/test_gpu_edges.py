@@ -179,3 +179,34 @@ def test_two_streams(B, H, dtype):
         assert s["layer"].check() == 0
         for got, ref in zip((s["y"], s["dx"], *s["grads"].values()), w):
             assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("B,H", [(384, 512), (512, 512), (300, 648), (512, 1024)])
+def test_row_blocks_in_flight_repeat(B, H):
+    """The copies of the next row block are issued into the LDS tile whose
+    fragments are being read, pair by pair; each must come after its pair's
+    reads.  Passes in a row are bitwise equal at every kernel's width."""
+    from paper_1907_13257_amd import Layer
+    T, I = 16, 64
+    announce(f"row blocks in flight B{B} H{H}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + H)
+
+    def uniform(*shape, dtype=torch.bfloat16):
+        return ((torch.rand(shape, generator=g, device="cuda") * 2 - 1) * H ** -0.5).to(dtype)
+
+    p = dict(W=uniform(4 * H, I), R=uniform(4 * H, H), b=uniform(4 * H, dtype=torch.float32))
+    x, dy = uniform(T, B, I), uniform(T, B, H)
+    lay = Layer(T, B, I, H, 0, "bf16")
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    grads = {"d" + k: torch.empty(v.shape, dtype=torch.float32, device="cuda") for k, v in p.items()}
+    want = None
+    for _ in range(6):
+        lay.forward(x, p["W"], p["R"], p["b"], y=y)
+        lay.backward(dy, x, p["W"], p["R"], y, grads, dx=dx)
+        assert lay.check() == 0
+        got = [v.clone() for v in (y, dx, *grads.values())]
+        if want is not None:
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+        want = got
+    lay.close()
