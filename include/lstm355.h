@@ -96,6 +96,9 @@ size_t lstm_workspace_size(lstm_handle_t h);
  *   x   [T][B][I] (stride ldx); h0 [B][Hr], c0 [B][H]: NULL means zeros.
  *   W, R, b, P: parameters; P must be NULL iff Hp == 0.
  *   y   [T][B][Ho] (stride ldy): h_t of every step, stored at time index t.
+ *       For bf16 plain layers of 256, 512 and 1024 cells (and in
+ *       lstm_forward_stack) no row of y may share memory with x or h0: the
+ *       library marks y before it has read them.
  *   hT, cT: final state (state after the last visited step), may be NULL.
  *   reserve: lstm_reserve_size bytes, kept for lstm_backward. */
 lstm_status_t lstm_forward(lstm_handle_t h,

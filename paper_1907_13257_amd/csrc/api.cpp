@@ -108,6 +108,32 @@ bool use_xcd(const lstm_handle *h, const RecShape &sh)
     return !(env && std::strcmp(env, "stepwise") == 0);
 }
 
+// Whether a row of `p` (`rows` rows of `width` elements, `ld` apart) shares
+// bytes with a row of y.  Rows interleaved at one stride in separate columns
+// (the two halves of a wider row) do not.
+bool overlaps_y(const lstm_handle *h, const void *p, long rows, long width, long ld, const void *y)
+{
+    if (!p) return false;
+    const long es = (long)h->es;
+    const long p0 = (long)reinterpret_cast<uintptr_t>(p), p1 = p0 + ((rows - 1) * ld + width) * es;
+    const long y0 = (long)reinterpret_cast<uintptr_t>(y), y1 = y0 + ((h->TB - 1) * h->ldy + h->Hr) * es;
+    if (p1 <= y0 || y1 <= p0) return false;
+    if (ld != h->ldy) return true;
+    const long stride = ld * es, col = ((p0 - y0) % stride + stride) % stride;   // p's columns within y's rows
+    return col < h->Hr * es || col + width * es > stride;
+}
+
+// The XCD-local forward marks all of y before the recurrence reads h0 and
+// while the input projection reads x.  A padded width whose x or h0 lies in y
+// (the state carried in y's last rows, a layer run in place) takes the generic
+// kernels instead, which write a row of y once its step's reads are done.
+bool forward_xcd(const lstm_handle *h, const RecShape &sh, const void *x, const void *h0, const void *y)
+{
+    if (!use_xcd(h, sh)) return false;
+    if (xcd_full_width(sh)) return true;   // these have always needed a y of its own
+    return !overlaps_y(h, x, h->TB, h->d.I, h->ldx, y) && !overlaps_y(h, h0, h->d.B, h->Hr, h->Hr, y);
+}
+
 #define TRY_HIP(what, expr)                                  \
     do {                                                     \
         hipError_t e_ = (expr);                              \
@@ -251,7 +277,7 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     fb.ms = d.Hp ? rv + h->r_ms : nullptr;
     fb.y = y; fb.hT = hT; fb.cT = cT;
     fb.sync = reinterpret_cast<unsigned *>(wv + h->w_sync);
-    const bool xcd = use_xcd(h, sh);
+    const bool xcd = forward_xcd(h, sh, x, h0, y);
     if (xcd && h->r_act16) fb.act16 = rv + h->r_act16;
 
     GemmDesc g{};
@@ -353,7 +379,7 @@ extern "C" lstm_status_t lstm_forward_noalloc(lstm_handle_t h, const void *x, co
         // sequence (wide LSTMP layers) needs split-K partials as well
         const lstm_desc_t &d = h->d;
         RecShape sh{d.T, d.B, d.I, d.H, d.Hp, d.reverse, h->ldy};
-        const bool stepwise = !use_xcd(h, sh) && use_stepwise(h, h->fwd_ok);
+        const bool stepwise = !forward_xcd(h, sh, x, h0, y) && use_stepwise(h, h->fwd_ok);
         const size_t need = stepwise ? h->w_split + h->split_floats * 4 : h->w_sync + SYNC_BYTES;
         if (need > NOALLOC_SCRATCH_BYTES) {
             std::snprintf(g_detail, sizeof(g_detail),

@@ -210,3 +210,44 @@ def test_row_blocks_in_flight_repeat(B, H):
             assert all(torch.equal(a, b) for a, b in zip(got, want))
         want = got
     lay.close()
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("T,B,H,share", [
+    (3, 9, 264, "h0 in y"),       # the state carried in the last rows of y
+    (4, 50, 648, "x is y"),       # the layer run in place
+    (2, 20, 136, "h0 in y"),
+    (3, 50, 648, "halves"),       # x and y interleaved: halves of one wider row
+])
+def test_inputs_inside_y(T, B, H, share, noalloc):
+    """A width without a kernel of its own takes x and h0 that lie in y's
+    memory (forward of two or more steps)."""
+    from paper_1907_13257_amd import Layer, lstm355
+    from _gpu_helpers import TOL, normwise, to_dev, to_f64
+    label = f"inputs inside y T{T} B{B} H{H} {share} noalloc{int(noalloc)}"
+    announce(label)
+    c = layer_case(T, B, H, H, 0, "bf16", False, seed=T + B + H, scale=H ** -0.5)
+    d = {k: to_dev(v) for k, v in c.items()}
+    wide = share == "halves"
+    buf = torch.empty((T, B, 2 * H if wide else H), dtype=torch.bfloat16, device="cuda")
+    x, h0, y = d["x"], d["h0"], buf[:, :, H:] if wide else buf
+    if share == "h0 in y":
+        h0 = y[T - 1]
+        h0.copy_(d["h0"])
+    else:
+        x = buf[:, :, :H]
+        x.copy_(d["x"])
+    hT = torch.empty((B, H), dtype=torch.bfloat16, device="cuda")
+    cT = torch.empty((B, H), dtype=torch.float32, device="cuda")
+    lay = Layer(T, B, H, H, 0, "bf16", ldx=2 * H if wide else 0, ldy=2 * H if wide else 0)
+    if noalloc:
+        lstm355.lstm_forward_noalloc(lay.handle, x, h0, d["c0"], d["W"], d["R"], d["b"], None, y, hT, cT,
+                                     lay.reserve)
+    else:
+        lay.forward(x, d["W"], d["R"], d["b"], h0=h0, c0=d["c0"], y=y, hT=hT, cT=cT)
+    assert lay.check() == 0
+    ref = oracle_layer(c, 0, False)
+    errs = {k: normwise(to_f64(v), ref[k]) for k, v in (("y", y.contiguous()), ("hT", hT), ("cT", cT))}
+    announce(f"{label} " + ", ".join(f"{k}={v:.2e}" for k, v in errs.items()))
+    assert max(errs.values()) <= TOL["bf16"]["out"], errs
+    lay.close()
