@@ -1573,6 +1573,9 @@ bool gemm_dual_ok(const GemmDesc &d)
     // without one, the second block runs over [ylo, yhi) alone
     if (d.B3 && (d.K % 32 || d.ylo % 32 || d.yhi % 32 || d.hlo % 32 || d.hlen % 32)) return false;
     if (d.B3 && (d.hlo < 0 || d.hlo + d.hlen > d.K)) return false;
+    // the second block's operands are addressed with 32-bit offsets too (y's
+    // rows may be strided far wider than the product)
+    if (d.b2_bytes > 0x7fffffffL || (d.B3 && d.b3_bytes > 0x7fffffffL)) return false;
     return dl_ok(d, 128, 128, 1);
 }
 

@@ -251,3 +251,37 @@ def test_inputs_inside_y(T, B, H, share, noalloc):
     announce(f"{label} " + ", ".join(f"{k}={v:.2e}" for k, v in errs.items()))
     assert max(errs.values()) <= TOL["bf16"]["out"], errs
     lay.close()
+
+
+@pytest.mark.parametrize("Hp,states", [(0, False), (0, True), (32, False)])
+def test_output_rows_spanning_more_than_2gib(Hp, states):
+    """y and dy strided so far apart that their last rows lie past 2 GiB:
+    every row of y still enters dR."""
+    from paper_1907_13257_amd import Layer
+    from _gpu_helpers import to_dev, to_f64
+    T, B, I, H = 64, 32, 64, 64
+    Hr, ld = Hp or H, 1 << 20
+    label = f"wide rows Hp{Hp} states{int(states)}"
+    announce(label)
+    c = layer_case(T, B, I, H, Hp, "bf16", False, seed=Hp + states, states=states, final_grads=states,
+                   scale=H ** -0.5)
+    d = {k: to_dev(v) for k, v in c.items()}
+    y = torch.empty((T, B, ld), dtype=torch.bfloat16, device="cuda")[:, :, :Hr]
+    dy = torch.empty((T, B, ld), dtype=torch.bfloat16, device="cuda")[:, :, :Hr]
+    dy.copy_(d["dy"])
+    f32 = dict(dtype=torch.float32, device="cuda")
+    grads = dict(dW=torch.empty((4 * H, I), **f32), dR=torch.empty((4 * H, Hr), **f32), db=torch.empty(4 * H, **f32))
+    if Hp:
+        grads["dP"] = torch.empty((Hp, H), **f32)
+    dx = torch.empty_like(d["x"])
+    lay = Layer(T, B, I, H, Hp, "bf16", ldy=ld)
+    lay.forward(d["x"], d["W"], d["R"], d["b"], d["P"], d["h0"], d["c0"], y)
+    lay.backward(dy, d["x"], d["W"], d["R"], y, grads, P=d["P"], h0=d["h0"], c0=d["c0"], dhT=d["dhT"],
+                 dcT=d["dcT"], dx=dx)
+    assert lay.check() == 0
+    gpu = {k: to_f64(v.contiguous()) for k, v in dict(grads, y=y, dx=dx).items()}
+    ref = oracle_layer(c, Hp, False)
+    for k in ("hT", "cT", "dh0", "dc0"):   # not asked for
+        gpu[k] = ref.get(k)
+    check_layer(gpu, {k: v for k, v in ref.items() if v is not None}, "bf16", label)
+    lay.close()
