@@ -111,12 +111,13 @@ lstm_status_t lstm_forward(lstm_handle_t h,
 /* lstm_forward without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  It calls no allocating routine: its
- * scratch (the sync words of the persistent recurrences: barrier counter,
- * abort word, per-XCD claim masks) lives in a 64 KiB array that the library
+ * scratch (the sync words of the persistent recurrences: abort words, step
+ * flags, per-XCD claim masks) lives in a 64 KiB array that the library
  * keeps on each GPU until the process ends.  Arguments and results are those
  * of lstm_forward.  Layers whose forward needs more scratch than that (the
- * stepwise recurrence of wide LSTMP layers, whose split products need
- * partial sums) return LSTM_ERR_WORKSPACE with the sizes in
+ * stepwise recurrence of LSTMP layers of 2048 cells and more, whose split
+ * products need partial sums, and layers wider than 8192 cells) return
+ * LSTM_ERR_WORKSPACE with the sizes in
  * lstm_last_error_detail.  Every call on one GPU shares its array, so calls
  * that overlap on one GPU (other streams, other threads) race and must be
  * ordered by the caller; each call clears what must start at zero. */

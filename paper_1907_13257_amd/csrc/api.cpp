@@ -87,8 +87,12 @@ lstm_status_t ensure_plan(lstm_handle *h)
 // Recurrence implementation for this handle: the persistent kernels keep
 // the recurrent weights on chip; the stepwise sequence streams them per step
 // and is used for LSTMP layers with wide cells (BigLSTM: 8192 cells) and
-// whenever no persistent tiling fits.  LSTM355_RECURRENCE=stepwise or
-// =persistent overrides the choice (testing and tuning).
+// whenever no persistent tiling fits (above 4096 cells: 256 workgroups of 16;
+// the former tilings of 32 cells were slower there than stepwise at every
+// size measured, per step and direction at H = 4104 and 1 row 47 / 26 us
+// forward and 156 / 62 backward, at H = 8192 and 200 rows 535 / 187 and
+// 915 / 369).  LSTM355_RECURRENCE=stepwise or =persistent overrides the choice
+// where both exist (testing and tuning).
 bool use_stepwise(const lstm_handle *h, bool persistent_ok)
 {
     const char *env = std::getenv("LSTM355_RECURRENCE");
@@ -303,7 +307,8 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     TRY_HIP("input projection", gemm(g, s, K_GEMM_GX));
 
     if (!xcd && use_stepwise(h, h->fwd_ok)) {
-        StepwiseArgs sw{R, P, reinterpret_cast<float *>(wv + h->w_split), h->split_floats};
+        StepwiseArgs sw{R, P, nullptr, 0};   // without the workspace: no product is split
+        if (full_ws) sw = StepwiseArgs{R, P, reinterpret_cast<float *>(wv + h->w_split), h->split_floats};
         TRY_HIP("forward recurrence (stepwise)", forward_stepwise(h->dt, sh, fb, sw, s));
     } else if (xcd) {
         TRY_HIP("forward recurrence (XCD-local)", launch_forward_xcd(sh, fb, watchdog_ticks(), s, true));
@@ -313,8 +318,8 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     return LSTM_OK;
 }
 
-// Scratch of lstm_forward_noalloc: the sync words (barrier counter, abort
-// word, per-XCD claim masks) that the persistent recurrences need, in a
+// Scratch of lstm_forward_noalloc: the sync words (abort words, step flags,
+// per-XCD claim masks) that the persistent recurrences need, in a
 // device array each GPU holds until the process ends.  Host code never uses
 // the array's name as an address: its device address is looked up once per
 // device with hipGetSymbolAddress and kept in g_scratch_ptr.
@@ -376,11 +381,14 @@ extern "C" lstm_status_t lstm_forward_noalloc(lstm_handle_t h, const void *x, co
         st = ensure_plan(h);
         if (st != LSTM_OK) return st;
         // the persistent recurrences need only the sync words; the stepwise
-        // sequence (wide LSTMP layers) needs split-K partials as well
+        // sequence of a wide LSTMP layer needs split-K partials.  A layer that
+        // is stepwise only because no persistent tiling fits (more than 4096
+        // cells, or rows strided too far apart) runs without splits.
         const lstm_desc_t &d = h->d;
         RecShape sh{d.T, d.B, d.I, d.H, d.Hp, d.reverse, h->ldy};
         const bool stepwise = !forward_xcd(h, sh, x, h0, y) && use_stepwise(h, h->fwd_ok);
-        const size_t need = stepwise ? h->w_split + h->split_floats * 4 : h->w_sync + SYNC_BYTES;
+        const bool unsplit = !h->fwd_ok && d.H <= 8192 && !(d.Hp > 0 && d.H >= 2048);
+        const size_t need = stepwise && !unsplit ? h->w_split + h->split_floats * 4 : h->w_sync + SYNC_BYTES;
         if (need > NOALLOC_SCRATCH_BYTES) {
             std::snprintf(g_detail, sizeof(g_detail),
                           "lstm_forward_noalloc: this layer needs %zu bytes of scratch, the library holds %zu "

@@ -656,13 +656,14 @@ static bool plan(bool fwd, DType t, const RecShape &sh, int num_cus, RecTiling *
     const long Kw = fwd ? Hr : (sh.Hp ? sh.Hp : 4L * sh.H);      // k of the resident slice
     const long Kd = fwd ? sh.H : 4L * sh.H;                      // k of the projection (LSTMP)
     const long ldmax = std::max<long>(sh.ldy, 4L * sh.H);
-    if (64 * ldmax * (long)es > 0x7fffffffL) return false;       // a tile's rows are addressed with 32-bit offsets
     bool found = false;
     double best = 0;
     for (int v = 0; v < NVAR; ++v) {
         const int MB = VAR_MB[v], NB = VAR_NB[v], HN = 4 * NB, BM = 16 * MB;
         const int nHT = (sh.H + HN - 1) / HN;
         if (nHT > num_cus || nHT > 256) continue;
+        // a tile's rows are addressed with 32-bit offsets
+        if ((std::min(BM, sh.B) * ldmax + std::max(Kw, Kd)) * (long)es > 0x7fffffffL) continue;
         const int nBT = (sh.B + BM - 1) / BM;
         const int bgroups = std::min(std::min(nBT, num_cus / nHT), MAX_BGROUPS);
         const int G = nHT * bgroups;

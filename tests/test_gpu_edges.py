@@ -285,3 +285,65 @@ def test_output_rows_spanning_more_than_2gib(Hp, states):
         gpu[k] = ref.get(k)
     check_layer(gpu, {k: v for k, v in ref.items() if v is not None}, "bf16", label)
     lay.close()
+
+
+# Plain layers without a persistent tiling: more than 4096 cells, or rows of y
+# strided so far apart that a tile's rows span more than 2 GiB:
+# (T, B, H, dtype, ldy)
+WIDE_NOALLOC_CASES = [
+    (3, 3, 4104, "bf16", 0),
+    (2, 33, 4608, "f32", 0),
+    (2, 130, 5000, "bf16", 0),
+    (2, 5, 8192, "f32", 0),
+    (2, 17, 72, "bf16", (1 << 24) + 8),   # still a persistent tiling, of 16 rows
+    (2, 16, 72, "bf16", 1 << 27),
+]
+
+
+@pytest.mark.parametrize("T,B,H,dtype,ldy", WIDE_NOALLOC_CASES)
+def test_noalloc_of_layers_without_a_persistent_tiling(T, B, H, dtype, ldy):
+    """lstm_forward_noalloc takes every plain layer of up to 8192 cells."""
+    from paper_1907_13257_amd import Layer, lstm355
+    from _gpu_helpers import TOL
+    label = f"noalloc wide T{T} B{B} H{H} {dtype} ldy{ldy}"
+    announce(label)
+    I = 16
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + B)
+
+    def uniform(*shape, dtype=td):
+        return ((torch.rand(shape, generator=g, device="cuda") * 2 - 1) * H ** -0.5).to(dtype)
+
+    W, R, b = uniform(4 * H, I), uniform(4 * H, H), uniform(4 * H, dtype=torch.float32)
+    x, h0, c0 = uniform(T, B, I), uniform(B, H), uniform(B, H, dtype=torch.float32)
+    lay = Layer(T, B, I, H, 0, dtype, ldy=ldy)
+    res = {}
+    for mode in ("workspace", "noalloc"):
+        y = torch.empty((T, B, ldy or H), dtype=td, device="cuda")[:, :, :H]
+        hT, cT = torch.empty_like(h0), torch.empty_like(c0)
+        if mode == "workspace":
+            lay.forward(x, W, R, b, None, h0, c0, y, hT, cT)
+        else:
+            lstm355.lstm_forward_noalloc(lay.handle, x, h0, c0, W, R, b, None, y, hT, cT, lay.reserve)
+        assert lay.check() == 0
+        res[mode] = dict(y=y.double(), hT=hT.double(), cT=cT.double())
+    h, c, ys = h0.double(), c0.double(), []
+    Wd, Rd = W.double(), R.double()
+    for t in range(T):
+        i, f, u, o = (x[t].double() @ Wd.t() + h @ Rd.t() + b.double()).chunk(4, dim=1)
+        c = torch.sigmoid(f) * c + torch.sigmoid(i) * torch.tanh(u)
+        h = torch.sigmoid(o) * torch.tanh(c)
+        ys.append(h)
+    ref = dict(y=torch.stack(ys), hT=h, cT=c)
+    for mode, got in res.items():
+        errs = {k: float((got[k] - ref[k]).abs().max() / ref[k].abs().max()) for k in ref}
+        announce(f"{label} {mode} " + ", ".join(f"{k}={v:.2e}" for k, v in errs.items()))
+        assert max(errs.values()) <= TOL[dtype]["out"], (mode, errs)
+    lay.close()
+
+
+@pytest.mark.parametrize("T,B,H,dtype,reverse", [(2, 3, 4104, "bf16", False), (2, 18, 4160, "f32", True)])
+def test_plain_layers_wider_than_the_persistent_kernels(T, B, H, dtype, reverse):
+    gpu = run_case(T, B, 24, H, 0, dtype, reverse, H ** -0.5)
+    assert gpu["tiling"][3] == 2000 and gpu["tiling"][7] == 2000, gpu["tiling"]
