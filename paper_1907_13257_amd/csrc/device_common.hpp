@@ -100,11 +100,14 @@ __device__ __forceinline__ u32x4 zero16() { return u32x4{0u, 0u, 0u, 0u}; }
 // wait for it before unrelated LDS accesses; callers order it themselves
 // with s_waitcnt vmcnt and barriers.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ u32x4 buffer_desc(const void *base, unsigned bytes)   // bytes: at most 2 GiB - 1
+{
+    const uintptr_t b = reinterpret_cast<uintptr_t>(base);
+    return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, bytes, 0x00020000u};
+}
 __device__ __forceinline__ u32x4 buffer_desc(const void *base, long bytes)
 {
-    const unsigned nrec = bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)bytes;
-    const uintptr_t b = reinterpret_cast<uintptr_t>(base);
-    return u32x4{(unsigned)b, (unsigned)(b >> 32) & 0xffffu, nrec, 0x00020000u};
+    return buffer_desc(base, bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)bytes);
 }
 
 __device__ __forceinline__ unsigned lds_addr(const void *p) { return (unsigned)(uintptr_t)p; }
