@@ -738,9 +738,9 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
     const int cr = tid / HN, cu = tid % HN, cj = j0 + cu;
     const bool has_cell = tid < NCELL && (!PAD || cj < H);
     __shared__ int s_bad;
-    if (tid == 0) s_bad = 0;   // ordered by the first barrier below
 
     if constexpr (MBX > 2) {
+        if (tid == 0) s_bad = 0;   // ordered by the first barrier below
         // Pipelined row blocks: see PipeRows.  The input projection of a block
         // is loaded one block ahead, before the copy of that block's rows.
         const PipeRows<RB, KCW, PAD> cp{rs_y, a.ldy, w * KW * 2, lane, slot, H * 2, tile, stage[w]};
@@ -879,6 +879,7 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
         const int b = row0 + mb * 16 + cr;
         creg[mb] = (has_cell && b < rowend && a.c0) ? a.c0[(long)b * H + cj] : 0.0f;
     }
+    if (tid == 0) s_bad = 0;   // ordered by the first barrier below
 
     int tprev = 0;
     for (int s = 0; s < a.T; ++s) {
@@ -1597,7 +1598,6 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
     };
     auto dc_init = [&](int b) { return (has_cell && b < rowend && a.dcT) ? a.dcT[(long)b * H + cj] : 0.0f; };
     __shared__ int s_bad;
-    if (tid == 0) s_bad = 0;   // ordered by the first barrier below
 
     // Gate gradients of one cell, from its inputs and the carries dh and
     // dc (replaced by the carry to the step before); z: the four before rounding.
@@ -1647,6 +1647,7 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
     };
 
     if constexpr (MBX > 2) {
+        if (tid == 0) s_bad = 0;   // ordered by the first barrier below
         // Pipelined row blocks: see PipeRows.  Block (s, mb) multiplies dz_s of
         // its rows into dh_{s-1} and goes on to their gate gradients at step
         // s - 1, whose inputs were loaded one block ahead.
@@ -1715,6 +1716,7 @@ __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
             dhn[mb] = dh_init(b);
             dcn[mb] = dc_init(b);
         }
+        if (tid == 0) s_bad = 0;   // ordered by the first barrier below
         for (int s = a.T - 1; s >= 0; --s) {
             const int t = a.reverse ? a.T - 1 - s : s;
             // gate gradients of the owned cells.  Every lane computes them (lanes
