@@ -103,13 +103,13 @@ bool use_stepwise(const lstm_handle *h, bool persistent_ok)
 }
 
 // Whether the layer runs on the XCD-local kernels: every shape they take,
-// except that LSTM355_RECURRENCE=stepwise (testing) still selects the
-// stepwise sequence for the widths that are padded.
+// except that LSTM355_RECURRENCE=stepwise and =persistent still select the
+// stepwise sequence and the generic kernels for the widths that are padded.
 bool use_xcd(const lstm_handle *h, const RecShape &sh)
 {
     if (!xcd_path_ok(h->dt, sh, h->num_cus)) return false;
     const char *env = xcd_full_width(sh) ? nullptr : std::getenv("LSTM355_RECURRENCE");
-    return !(env && std::strcmp(env, "stepwise") == 0);
+    return !(env && (std::strcmp(env, "stepwise") == 0 || std::strcmp(env, "persistent") == 0));
 }
 
 // Whether a row of `p` (`rows` rows of `width` elements, `ld` apart) shares

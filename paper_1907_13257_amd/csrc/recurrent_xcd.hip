@@ -1844,6 +1844,14 @@ bool xcd_act16(DType t, const RecShape &sh)
     return RX >= 5 && RX <= 32;
 }
 
+// Every width up to 1024: the widths that are padded beat the generic kernels
+// at nearly every size measured (8 to 1016 cells, 1 to 512 rows; a layer's
+// forward and its backward, T = 30, padded / generic): H = 264, 1 row 62 + 71 /
+// 103 + 152 us, 64 rows 72 + 103 / 136 + 195, 512 rows 225 + 343 / 270 + 429;
+// H = 520, 64 rows 94 + 126 / 161 + 238; H = 1016, 512 rows 394 + 663 / 1030 +
+// 1531.  The generic kernels are ahead only where a few cells meet many rows:
+// H = 8, 512 rows 174 + 246 / 101 + 171, H = 64, 512 rows 185 + 256 / 154 + 251
+// (from H = 200 on not any more); no rule for those yet.
 bool xcd_path_ok(DType t, const RecShape &sh, int num_cus)
 {
     if (g_xcd_disabled || t != DType::BF16 || sh.Hp != 0 || num_cus != NXCD * WG_PER_XCD) return false;

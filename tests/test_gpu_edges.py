@@ -347,3 +347,13 @@ def test_noalloc_of_layers_without_a_persistent_tiling(T, B, H, dtype, ldy):
 def test_plain_layers_wider_than_the_persistent_kernels(T, B, H, dtype, reverse):
     gpu = run_case(T, B, 24, H, 0, dtype, reverse, H ** -0.5)
     assert gpu["tiling"][3] == 2000 and gpu["tiling"][7] == 2000, gpu["tiling"]
+
+
+@pytest.mark.parametrize("recurrence,variants", [("persistent", None), ("stepwise", (2000,))])
+def test_recurrence_switch_at_padded_widths(recurrence, variants, monkeypatch):
+    """LSTM355_RECURRENCE selects the generic kernels and the stepwise sequence
+    for the widths that the XCD-local kernels pad."""
+    monkeypatch.setenv("LSTM355_RECURRENCE", recurrence)
+    gpu = run_case(3, 21, 40, 264, 0, "bf16", False, 264 ** -0.5)
+    got = {gpu["tiling"][3], gpu["tiling"][7]}
+    assert got == set(variants) if variants else not got & {1000, 1001, 2000}, gpu["tiling"]
