@@ -1172,11 +1172,21 @@ int f32_splits(const GemmDesc &d)
     return best;
 }
 
+// Tile and split choice of the bf16 products (below); a tuning override's split
+// count holds for the fp32 products as well.
+struct Choice {
+    int tile;
+    int splits;
+};
+bool env_choice(Choice *c);
+int fit_splits(const GemmDesc &d, int want);
+
 template <bool AK, bool BKM>
 hipError_t launch_gemm_f32(const GemmDesc &d, hipStream_t s)
 {
     GemmArgs g{};
-    int splits = f32_splits(d);
+    Choice c;
+    int splits = env_choice(&c) && c.splits > 0 ? fit_splits(d, c.splits) : f32_splits(d);
     g.M = d.M; g.N = d.N; g.K = d.K;
     g.A = static_cast<const char *>(d.A); g.lda = d.lda;
     g.B = static_cast<const char *>(d.B); g.ldb = d.ldb;
@@ -1196,13 +1206,6 @@ hipError_t launch_gemm_f32(const GemmDesc &d, hipStream_t s)
     if (e != hipSuccess || splits == 1) return e;
     return launch_splitk_reduce<float>(d, splits, s);
 }
-
-// Tile and split choice: a crude model of per-CU efficiency per tile shape,
-// quantised over 256 CUs, plus the traffic of the split-K partials.
-struct Choice {
-    int tile;     // 0: 256x256, 1: 256x128, 2: 128x256, 3: 128x128
-    int splits;
-};
 
 // Tile configurations of the direct-to-LDS kernel (bf16):
 //   index: BM x BN, waves (NWM x NWN), k per stage, ring stages
@@ -1234,7 +1237,6 @@ const int kTileSlots[NTILES] = {1, 1, 1, 2, 1, 2, 1, 1, 1, 1, 1, 2, 2, 1, 1, 1, 
 
 bool dl_ok(const GemmDesc &d, int BM, int BN, int splits);
 bool tile_fits(const GemmDesc &d, int t);
-bool env_choice(Choice *c);
 
 // Split count for tile shape BM x BN with `slots` workgroups per CU: enough
 // k splits to fill the CUs, against the cost of the fp32 partials.
@@ -1259,6 +1261,8 @@ int model_splits(const GemmDesc &d, int BM, int BN, int slots, int kd)
     return best;
 }
 
+// Tile and split choice: a crude model of per-CU efficiency per tile shape,
+// quantised over 256 CUs, plus the traffic of the split-K partials.
 Choice choose(const GemmDesc &d, size_t es)
 {
     static const int BMs[4] = {256, 256, 128, 128}, BNs[4] = {256, 128, 256, 128};
@@ -1488,7 +1492,8 @@ bool tile_fits(const GemmDesc &d, int t)
     return dl_ok(d, kTileBM[t], kTileBN[t], 1);
 }
 
-// Tuning override from the environment: "tile" or "tile,splits", in
+// Tuning override from the environment: "tile" or "tile,splits" (fp32 products
+// have one tile and take the split count), in
 // LSTM355_GEMM_TILE_<class number> for one kernel class, else
 // LSTM355_GEMM_TILE for every product.
 thread_local int g_kclass = -1;

@@ -357,3 +357,18 @@ def test_recurrence_switch_at_padded_widths(recurrence, variants, monkeypatch):
     gpu = run_case(3, 21, 40, 264, 0, "bf16", False, 264 ** -0.5)
     got = {gpu["tiling"][3], gpu["tiling"][7]}
     assert got == set(variants) if variants else not got & {1000, 1001, 2000}, gpu["tiling"]
+
+
+def test_split_override_of_fp32_products(monkeypatch):
+    """LSTM355_GEMM_TILE's split count reaches the fp32 products: another order
+    of the sums over k, the same gradients within fp32 rounding."""
+    T, B, I, H = 40, 33, 264, 136
+    c = layer_case(T, B, I, H, 0, "f32", False, seed=5, scale=I ** -0.5)
+    ref = oracle_layer(c, 0, False)
+    got = []
+    for override in ("3,1", "3,4"):
+        monkeypatch.setenv("LSTM355_GEMM_TILE", override)
+        announce(f"fp32 products, tile override {override}")
+        got.append(run_layer_gpu(c, T, B, I, H, 0, "f32", False))
+        check_layer(got[-1], ref, "f32", f"override {override}")
+    assert not (got[0]["dW"] == got[1]["dW"]).all()
