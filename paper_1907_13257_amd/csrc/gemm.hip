@@ -2,15 +2,19 @@
 // matrix cores: the input projection X W^T + b for all T steps at once, and
 // the gradients dX = dZ W, dW = dZ^T X, dR = dZ^T H_prev, dP = dH^T M.
 //
-// One kernel template covers all of them.  A workgroup (4 waves, 2x2) owns a
-// BM x BN tile of C (up to 256x256: 128x128 per wave, accumulators in AGPRs)
-// and walks K in stages of KB bytes per row.  Both operands are staged in LDS
-// with k contiguous in every row, so every fragment read is a 16-byte
-// ds_read.  An operand whose k is not the contiguous dimension in memory (the
-// transposed operands of the weight gradients) is loaded with 16-byte global
-// reads along m and transposed in registers before the LDS write.  Two LDS
-// stages: the global loads of stage s+1 are in flight while stage s feeds
-// v_mfma_f32_32x32x16_bf16 (fp32 inputs: v_mfma_f32_32x32x2f32).
+// Three kernels, all on tiles of C whose operands pass through LDS:
+//   gemm_dl_kernel   bf16: tiles of 64x64 to 256x256, operands loaded straight
+//                    into LDS (v_mfma_f32_32x32x16_bf16);
+//   gemm_f32_kernel  fp32: 64x64 tiles, loaded the same way
+//                    (v_mfma_f32_32x32x2f32);
+//   gemm_kernel      either type, for operands of more than 2 GiB, past what the
+//                    others' 32-bit offsets reach: staged through registers.
+//                    A workgroup (4 waves, 2x2) owns a BM x BN tile and walks K
+//                    in stages of KB bytes per row, k contiguous in every LDS
+//                    row; an operand whose k is not the contiguous dimension in
+//                    memory is loaded with 16-byte reads along m and transposed
+//                    in registers.  Two LDS stages: the loads of stage s+1 are
+//                    in flight while stage s feeds the matrix cores.
 //
 // Small outputs (the weight gradients are 4H x I at most, K = T*B long) can
 // be split along K over several workgroups; every split writes an fp32
@@ -1136,9 +1140,18 @@ hipError_t launch_gemm(const GemmDesc &d, int splits, hipStream_t s)
     return launch_splitk_reduce<TO>(d, splits, s);
 }
 
+// LSTM355_GEMM_DL=0 (testing) sends every product to the register-staged kernel,
+// which only operands of more than 2 GiB reach otherwise.
+bool dma_disabled()
+{
+    const char *env = std::getenv("LSTM355_GEMM_DL");
+    return env && env[0] == '0';
+}
+
 // The fp32 kernel addresses operands with 32-bit byte offsets, in 16-byte chunks.
 bool f32_ok(const GemmDesc &d)
 {
+    if (dma_disabled()) return false;
     if (d.K % 4 && (d.a_kmajor || d.b_kmajor)) return false;
     if (d.lda % 4 || d.ldb % 4 || d.nbatch > 1 || d.N1 > 0 || d.partials > 1) return false;
     const long ea = d.a_kmajor ? (long)d.M * d.lda : (long)d.K * d.lda;
@@ -1235,7 +1248,7 @@ const int kTileKD[NTILES] = {32, 32, 32, 32, 32, 64, 64, 64, 64, 32, 64, 32, 32,
 // Workgroups of each configuration that fit on one CU (LDS-limited).
 const int kTileSlots[NTILES] = {1, 1, 1, 2, 1, 2, 1, 1, 1, 1, 1, 2, 2, 1, 1, 1, 1, 1, 2, 2, 2, 1, 1, 1, 1};
 
-bool dl_ok(const GemmDesc &d, int BM, int BN, int splits);
+bool dl_ok(const GemmDesc &d);
 bool tile_fits(const GemmDesc &d, int t);
 
 // Split count for tile shape BM x BN with `slots` workgroups per CU: enough
@@ -1275,7 +1288,7 @@ Choice choose(const GemmDesc &d, size_t es)
             return c;
         }
     }
-    if (es == 2 && d.M <= 256 && dl_ok(d, 128, 128, 1)) {
+    if (es == 2 && d.M <= 256 && dl_ok(d)) {
         // skinny products (one step of the stepwise recurrence) stream their
         // weight operand once.  Measured on the wide LSTMP layer's per-step
         // shapes (M = 128): accumulating with a k-contiguous weight, 128x64
@@ -1337,14 +1350,14 @@ Choice choose(const GemmDesc &d, size_t es)
         const long tiles = (long)((d.M + 255) / 256) * ((d.N + 255) / 256);
         if (tiles >= 192) return Choice{22, 1};
     }
-    if (es == 2 && d.a_kmajor && d.b_kmajor && dl_ok(d, 128, 256, 1)) {
+    if (es == 2 && d.a_kmajor && d.b_kmajor && dl_ok(d)) {
         // both operands k-contiguous (the input projection): 128x256 tiles of
         // 8 waves move less L2 traffic per flop than 128x128 once they fill
         // the 512 workgroup slots at least once
         const long tiles = (long)((d.M + 127) / 128) * ((d.N + 255) / 256);
         if (tiles >= 512) return Choice{2, 1};
     }
-    if (es == 2 && dl_ok(d, 128, 128, 1)) {
+    if (es == 2 && dl_ok(d)) {
         // direct-to-LDS 128x128 tiles run two workgroups per CU (512 slots);
         // split K only to fill the slots.  dX's layout takes 64-deep stages in
         // a ring of two (B = 128 65.6 -> 64.1 us, B = 64 44.8 -> 42.7 us), the
@@ -1395,19 +1408,14 @@ Choice choose(const GemmDesc &d, size_t es)
 // reach past M and N: of a k-major operand those rows lie past its bounds and
 // read zero, of an m-major one those columns are the next row's first ones;
 // either feeds only outputs that are not stored.
-bool dl_ok(const GemmDesc &d, int BM, int BN, int splits)
+bool dl_ok(const GemmDesc &d)
 {
-    const char *env = std::getenv("LSTM355_GEMM_DL");
-    if (env && env[0] == '0') return false;
-    (void)BM;
-    (void)BN;
+    if (dma_disabled()) return false;
     if (d.K % 8 && (d.a_kmajor || d.b_kmajor)) return false;
     if (d.lda % 8 || d.ldb % 8) return false;
     const long ea = d.a_kmajor ? (long)d.M * d.lda : (long)d.K * d.lda;
     const long eb = d.b_kmajor ? (long)d.N * d.ldb : (long)d.K * d.ldb;
-    if (ea * 2 > 0x7fffffffL || eb * 2 > 0x7fffffffL) return false;
-    (void)splits;
-    return true;
+    return ea * 2 <= 0x7fffffffL && eb * 2 <= 0x7fffffffL;
 }
 
 // Largest split count <= want whose fp32 partials fit the caller's split-K workspace.
@@ -1489,7 +1497,7 @@ bool tile_fits(const GemmDesc &d, int t)
     if ((!d.a_kmajor && kTileBM[t] < 128) || (!d.b_kmajor && kTileBN[t] < 128)) return false;
     if (d.N1 > 0 && d.B3 && (d.ylo % kd || d.yhi % kd || d.hlo % kd || d.hlen % kd))
         return false;   // stages stay in one segment
-    return dl_ok(d, kTileBM[t], kTileBN[t], 1);
+    return dl_ok(d);
 }
 
 // Tuning override from the environment: "tile" or "tile,splits" (fp32 products
@@ -1554,7 +1562,7 @@ hipError_t dispatch_tiles(const GemmDesc &d, hipStream_t s)
         return launch_gemm<TI, TO, 128, 128, 64, AK, BKM>(d, c.splits, s);
     } else {
         if (tile_fits(d, c.tile)) return launch_tile<TO, AK, BKM>(c.tile, d, c.splits, s);
-        if (dl_ok(d, 128, 128, c.splits)) return launch_tile<TO, AK, BKM>(3, d, c.splits, s);
+        if (dl_ok(d)) return launch_tile<TO, AK, BKM>(3, d, c.splits, s);
         switch (c.tile) {
         case 0: return launch_gemm<TI, TO, 256, 256, 128, AK, BKM>(d, c.splits, s);
         case 1: return launch_gemm<TI, TO, 256, 128, 128, AK, BKM>(d, c.splits, s);
@@ -1590,7 +1598,7 @@ bool gemm_dual_ok(const GemmDesc &d)
     // the second block's operands are addressed with 32-bit offsets too (y's
     // rows may be strided far wider than the product)
     if (d.b2_bytes > 0x7fffffffL || (d.B3 && d.b3_bytes > 0x7fffffffL)) return false;
-    return dl_ok(d, 128, 128, 1);
+    return dl_ok(d);
 }
 
 // One product saves the other's launch, its reads of A and both split-K
@@ -1616,7 +1624,7 @@ bool gemm_cell_ok(const GemmDesc &d)
 {
     if (d.cell_h <= 0 || d.in != DType::BF16 || !d.a_kmajor || !d.b_kmajor || !d.out_f32 || !d.beta) return false;
     if (d.N1 > 0 || d.bias || !d.cell_c || !d.cell_m || d.N != 4 * d.cell_h || d.cell_h % 16 || d.K % 64) return false;
-    return dl_ok(d, 128, 64, 1);
+    return dl_ok(d);
 }
 
 hipError_t gemm(const GemmDesc &d, hipStream_t s, int kclass)

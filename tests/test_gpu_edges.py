@@ -372,3 +372,14 @@ def test_split_override_of_fp32_products(monkeypatch):
         got.append(run_layer_gpu(c, T, B, I, H, 0, "f32", False))
         check_layer(got[-1], ref, "f32", f"override {override}")
     assert not (got[0]["dW"] == got[1]["dW"]).all()
+
+
+@pytest.mark.parametrize("dtype,tile", [("bf16", "0,1"), ("bf16", "1,3"), ("bf16", "2,1"), ("bf16", "3,4"),
+                                        ("f32", "3,1"), ("f32", "3,4")])
+def test_register_staged_products(dtype, tile, monkeypatch):
+    """The products' kernel for operands past 2 GiB, at every tile, with and
+    without splits: ragged sides, accumulation, states."""
+    monkeypatch.setenv("LSTM355_GEMM_DL", "0")
+    monkeypatch.setenv("LSTM355_GEMM_TILE", tile)
+    run_case(9, 61, 328, 264, 0, dtype, False, 328 ** -0.5)
+    run_case(5, 33, 136, 72, 40, dtype, True, 136 ** -0.5)
