@@ -70,9 +70,9 @@ def test_pipelined_row_blocks(T, B, H, reverse, states):
 
 
 # Generic persistent kernels (fp32, LSTMP, bf16 wider than 1024): (T, B, I, H,
-# Hp, dtype, reverse, states).  Between them the planned tilings have 1 and 2
-# row blocks per tile and several tiles per workgroup, weights in LDS and
-# streamed, projections with fewer and with more column blocks than workgroups.
+# Hp, dtype, reverse, states).  Between them tiles of 16 and 32 rows, weights in
+# LDS and streamed, projections with fewer and with more column blocks than
+# workgroups; several tiles per workgroup and tiles of 64 rows are below.
 GENERIC_CASES = [
     (3, 1, 8, 8, 0, "f32", False, True),
     (4, 16, 24, 256, 0, "f32", True, True),       # whole tiles
@@ -88,7 +88,7 @@ GENERIC_CASES = [
     (3, 65, 24, 520, 136, "bf16", False, False),
     (2, 19, 24, 1800, 256, "bf16", False, True),
     (2, 36, 24, 640, 320, "f32", True, True),
-    (3, 300, 24, 64, 32, "bf16", False, True),    # several tiles per workgroup
+    (3, 300, 24, 64, 32, "bf16", False, True),    # ten tiles of 32 rows, eight shares of the projection
 ]
 
 
@@ -96,6 +96,36 @@ GENERIC_CASES = [
 def test_generic_kernels(T, B, I, H, Hp, dtype, reverse, states):
     gpu = run_case(T, B, I, H, Hp, dtype, reverse, min(0.3, H ** -0.5), states)
     assert gpu["tiling"][3] not in (1000, 1001, 2000), gpu["tiling"]
+
+
+# Generic tilings with several tiles per workgroup (carries through memory, a
+# projection's share striding over the group's tiles) or 64-row tiles, and bf16
+# plain layers of more than 512 rows: the case as above, then per direction
+# (rows per tile, tiles per workgroup, slice in LDS, projection in LDS)
+GENERIC_TILINGS = [
+    ((3, 96, 24, 1024, 512, "bf16", False, True), (16, 2, 1, 1), (16, 2, 1, 1)),
+    ((2, 128, 24, 1504, 512, "bf16", True, True), (16, 4, 1, 1), (32, 4, 1, 0)),
+    ((2, 96, 16, 1024, 512, "f32", False, True), (16, 3, 1, 1), (16, 2, 1, 0)),
+    ((2, 64, 16, 1800, 768, "f32", True, False), (16, 2, 0, 1), (16, 2, 1, 0)),   # a streamed slice of R
+    ((3, 600, 24, 200, 64, "f32", True, True), (32, 2, 1, 1), (16, 3, 1, 1)),
+    ((3, 1100, 16, 40, 24, "bf16", False, True), (64, 2, 1, 1), (64, 2, 1, 1)),
+    ((2, 600, 16, 72, 0, "bf16", False, True), (64, 1, 1, 0), (64, 1, 1, 0)),
+    ((3, 1100, 16, 40, 0, "bf16", True, True), (64, 2, 1, 0), (64, 2, 1, 0)),
+    ((3, 700, 16, 16, 0, "f32", False, True), (64, 1, 1, 0), (64, 1, 1, 0)),
+    ((2, 530, 16, 1024, 0, "bf16", False, False), (32, 9, 1, 0), (16, 9, 1, 0)),
+]
+
+
+@pytest.mark.parametrize("case,fwd,bwd", GENERIC_TILINGS)
+def test_generic_tilings(case, fwd, bwd):
+    T, B, I, H, Hp, dtype, reverse, states = case
+    gpu = run_case(T, B, I, H, Hp, dtype, reverse, min(0.3, H ** -0.5), states)
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        return
+    for (groups, cells, rows, variant), want in ((gpu["tiling"][:4], fwd), (gpu["tiling"][4:], bwd)):
+        bgroups = groups // -(-H // cells)
+        tiles = -(-(-(-B // rows)) // bgroups)
+        assert (rows, tiles, variant >> 8 & 1, variant >> 9 & 1) == want, gpu["tiling"]
 
 
 # Time-parallel products off their tiles: widths that are no multiple of a

@@ -49,7 +49,8 @@ def forward_both(T, B, I, H, dtype, seed):
 
 @pytest.mark.parametrize("dtype,first,second", [
     ("bf16", (6, 40, 64, 256), (3, 9, 32, 256)),     # XCD-local recurrence, then a smaller layer
-    ("f32", (5, 37, 40, 72), (2, 5, 16, 40)),        # generic persistent recurrence (grid barrier)
+    ("bf16", (6, 50, 64, 648), (3, 9, 32, 264)),     # the same at padded widths
+    ("f32", (5, 37, 40, 72), (2, 5, 16, 40)),        # generic persistent recurrence (step flags)
 ])
 def test_noalloc_forward_matches_workspace_forward(dtype, first, second):
     for i, (T, B, I, H) in enumerate((first, second)):
