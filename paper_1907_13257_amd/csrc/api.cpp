@@ -84,22 +84,43 @@ lstm_status_t ensure_plan(lstm_handle *h)
     return LSTM_OK;
 }
 
-// Recurrence implementation for this handle: the persistent kernels keep
-// the recurrent weights on chip; the stepwise sequence streams them per step
-// and is used for LSTMP layers with wide cells (BigLSTM: 8192 cells) and
-// whenever no persistent tiling fits (above 4096 cells: 256 workgroups of 16;
-// the former tilings of 32 cells were slower there than stepwise at every
-// size measured, per step and direction at H = 4104 and 1 row 47 / 26 us
-// forward and 156 / 62 backward, at H = 8192 and 200 rows 535 / 187 and
-// 915 / 369).  LSTM355_RECURRENCE=stepwise or =persistent overrides the choice
-// where both exist (testing and tuning).
-bool use_stepwise(const lstm_handle *h, bool persistent_ok)
+// Recurrence of a direction: the persistent kernels keep the recurrent
+// weights on chip; the stepwise sequence streams them per step.
+// LSTM355_RECURRENCE=stepwise or =persistent overrides the choice where both
+// exist (testing and tuning).  Stepwise runs
+//   - what has no persistent tiling: above 4096 cells (256 workgroups of 16; the
+//     former tilings of 32 cells were slower there than stepwise at every size
+//     measured, per step at H = 4104 and 1 row 47 / 26 us forward and 156 / 62
+//     backward, at H = 8192 and 200 rows 535 / 187 and 915 / 369), and rows
+//     strided too far apart;
+//   - LSTMP layers with wide cells (BigLSTM: 8192 cells);
+//   - plain layers whose workgroups work through their tiles one after another
+//     while a product of the whole step fills the chip.  Persistent / stepwise,
+//     I = 256: the slice of R read from memory again for every tile, forward
+//     from three tiles on (bf16 H = 2560, 128 rows, T = 6: eight tiles 646 / 186
+//     us; three tiles 1.3 to 1.8 times slower, two 0.9 to 1.6, one faster) and
+//     backward from four on (H = 2560, 320 rows, T = 6: 2194 / 426; four tiles
+//     1.5 to 2.9 times slower); the slice on chip, forward, from 14 tiles on
+//     (fp32 H = 512, 6000 rows, T = 20: 5367 / 3260; 1.1 to 1.8 times slower;
+//     13 tiles 0.9 to 1.3) and for fewer than 128 cells from six on (H = 64,
+//     12000 rows, T = 2: 110 / 66);
+//   - a forward of one step, which exchanges nothing: bf16 H = 1536, 200 rows 65
+//     / 27 us, fp32 H = 64, 33 rows 26 / 14; except one streamed tile, where the
+//     product leaves most of the chip idle (fp32 H = 4096, 1 row 81 / 104).
+bool use_stepwise(const lstm_handle *h, bool fwd)
 {
+    const bool ok = fwd ? h->fwd_ok : h->bwd_ok;
     const char *env = std::getenv("LSTM355_RECURRENCE");
     if (env && std::strcmp(env, "stepwise") == 0) return true;
-    if (env && std::strcmp(env, "persistent") == 0 && persistent_ok) return false;
-    if (!persistent_ok) return true;
-    return h->d.Hp > 0 && h->d.H >= 2048;
+    if (!ok) return true;
+    if (env && std::strcmp(env, "persistent") == 0) return false;
+    if (h->d.Hp > 0) return h->d.H >= 2048;
+    const RecTiling &t = fwd ? h->fwd : h->bwd;
+    const int tiles = (t.nBT + t.bgroups - 1) / t.bgroups;   // of one workgroup
+    const bool streamed = !((t.variant >> 8) & 1);
+    if (!fwd) return streamed && tiles >= 4;
+    if (h->d.T == 1) return !streamed || tiles >= 2;
+    return streamed ? tiles >= 3 : tiles >= (h->d.H < 128 ? 6 : 14);
 }
 
 // Whether the layer runs on the XCD-local kernels: every shape they take,
@@ -306,7 +327,7 @@ lstm_status_t forward_impl(lstm_handle_t h, const void *x, const void *h0, const
     }
     TRY_HIP("input projection", gemm(g, s, K_GEMM_GX));
 
-    if (!xcd && use_stepwise(h, h->fwd_ok)) {
+    if (!xcd && use_stepwise(h, true)) {
         StepwiseArgs sw{R, P, nullptr, 0};   // without the workspace: no product is split
         if (full_ws) sw = StepwiseArgs{R, P, reinterpret_cast<float *>(wv + h->w_split), h->split_floats};
         TRY_HIP("forward recurrence (stepwise)", forward_stepwise(h->dt, sh, fb, sw, s));
@@ -380,14 +401,13 @@ extern "C" lstm_status_t lstm_forward_noalloc(lstm_handle_t h, const void *x, co
         if (st != LSTM_OK) return st;
         st = ensure_plan(h);
         if (st != LSTM_OK) return st;
-        // the persistent recurrences need only the sync words; the stepwise
-        // sequence of a wide LSTMP layer needs split-K partials.  A layer that
-        // is stepwise only because no persistent tiling fits (more than 4096
-        // cells, or rows strided too far apart) runs without splits.
+        // the persistent recurrences need only the sync words, and a plain
+        // layer's stepwise sequence runs without splits; that of a wide LSTMP
+        // layer needs its split-K partials
         const lstm_desc_t &d = h->d;
         RecShape sh{d.T, d.B, d.I, d.H, d.Hp, d.reverse, h->ldy};
-        const bool stepwise = !forward_xcd(h, sh, x, h0, y) && use_stepwise(h, h->fwd_ok);
-        const bool unsplit = !h->fwd_ok && d.H <= 8192 && !(d.Hp > 0 && d.H >= 2048);
+        const bool stepwise = !forward_xcd(h, sh, x, h0, y) && use_stepwise(h, true);
+        const bool unsplit = d.H <= 8192 && (d.Hp == 0 || d.H < 2048);
         const size_t need = stepwise && !unsplit ? h->w_split + h->split_floats * 4 : h->w_sync + SYNC_BYTES;
         if (need > NOALLOC_SCRATCH_BYTES) {
             std::snprintf(g_detail, sizeof(g_detail),
@@ -701,8 +721,9 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
 
         RecShape sh{T, B, I, H, Hp, d.reverse, h->ldy};
         const bool xcd = use_xcd(h, sh);
-        const bool stepwise = !xcd && use_stepwise(h, h->bwd_ok);
-        const int db_rows = xcd ? 8 : h->bwd.bgroups;   // partial bias gradients of a persistent recurrence
+        const bool stepwise = !xcd && use_stepwise(h, false);
+        // partial bias gradients of the recurrence (none: a stepwise LSTMP layer)
+        const int db_rows = xcd ? 8 : !stepwise ? h->bwd.bgroups : Hp ? 0 : stepwise_db_rows(B);
 
         BwdBufs bb{};
         bb.Rt = Rt; bb.Pt = Pt; bb.dy = dy; bb.dhT = dhT; bb.dcT = dcT; bb.h0 = h0; bb.c0 = c0;
@@ -761,7 +782,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
             }
             g.hlen = B;
             g.C2 = dR; g.ldc2 = Hr;
-            if (!stepwise) {   // db = sum of the recurrence's partials, done by the same launch
+            if (db_rows) {   // db = sum of the recurrence's partials, done by the same launch
                 g.side.sum_src = reinterpret_cast<const float *>(wv + h->w_part);
                 g.side.sum_rows = db_rows;
                 g.side.sum_cols = (int)G4;
@@ -817,7 +838,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
             }
             if (!beta) TRY_HIP("dR zero", fill_u32(dR, (size_t)G4 * Hr, 0u, s));
         }
-        if (!stepwise) {   // fp32 partials per XCD or batch group (the fused product sums them itself)
+        if (db_rows) {   // fp32 partials (the fused product sums them itself)
             if (!fused)
                 TRY_HIP("db", sum_rows(reinterpret_cast<const float *>(wv + h->w_part), db_rows, (int)G4, db,
                                        accumulate, s));
@@ -880,12 +901,6 @@ extern "C" lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8)
     if (st != LSTM_OK) return st;
     RecShape sh{h->d.T, h->d.B, h->d.I, h->d.H, h->d.Hp, h->d.reverse, h->ldy};
     const bool xcd = use_xcd(h, sh);
-    if (!xcd && use_stepwise(h, h->fwd_ok && h->bwd_ok)) {
-        // stepwise sequence: GEMM launches per step, no persistent grid
-        const int v[8] = {0, 0, h->d.B, STEPWISE_VARIANT, 0, 0, h->d.B, STEPWISE_VARIANT};
-        for (int i = 0; i < 8; ++i) out8[i] = v[i];
-        return LSTM_OK;
-    }
     if (xcd) {
         // XCD-local kernels: 256 workgroups, 8, 16 or 32 cells each, ceil(B/8) rows per XCD
         const int rx = (h->d.B + 7) / 8;
@@ -895,13 +910,10 @@ extern "C" lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8)
         for (int i = 0; i < 8; ++i) out8[i] = v[i];
         return LSTM_OK;
     }
-    out8[0] = h->fwd_ok ? h->fwd.G : 0;
-    out8[1] = h->fwd.HN;
-    out8[2] = h->fwd.BM;
-    out8[3] = h->fwd.variant;
-    out8[4] = h->bwd_ok ? h->bwd.G : 0;
-    out8[5] = h->bwd.HN;
-    out8[6] = h->bwd.BM;
-    out8[7] = h->bwd.variant;
+    // stepwise sequence: GEMM launches per step, no persistent grid
+    const RecTiling step{0, h->d.B, 0, 0, 0, 0, STEPWISE_VARIANT, 0};
+    const RecTiling &f = use_stepwise(h, true) ? step : h->fwd, &b = use_stepwise(h, false) ? step : h->bwd;
+    const int v[8] = {f.G, f.HN, f.BM, f.variant, b.G, b.HN, b.BM, b.variant};
+    for (int i = 0; i < 8; ++i) out8[i] = v[i];
     return LSTM_OK;
 }

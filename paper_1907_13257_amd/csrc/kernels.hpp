@@ -159,6 +159,13 @@ hipError_t gates_backward(DType t, int B, int H, const float *dm, const void *dy
                           const void *dhT, const float *gates_t, const float *c_t, const float *cprev, float *dcn,
                           void *dz_t, float *dc0, int kclass, hipStream_t s);
 
+// The same for a plain layer's step, which also sums dz over the rows in fp32:
+// dbpart [stepwise_db_rows(B)][4H], stored when `first`, else added to.
+hipError_t gates_backward_db(DType t, int B, int H, const void *dy, long ldy, const float *dh, const void *dhT,
+                             const float *gates_t, const float *c_t, const float *cprev, float *dcn, void *dz_t,
+                             float *dc0, float *dbpart, int first, int kclass, hipStream_t s);
+inline int stepwise_db_rows(int B) { return B >= 64 ? 16 : (B + 3) / 4; }   // at most MAX_BGROUPS
+
 // Persistent recurrence kernels (recurrent.hip).
 struct RecShape {
     int T, B, I, H, Hp, reverse;
@@ -213,7 +220,8 @@ struct BwdBufs {
     float *dhn;         // [B][H] carry of dh between steps (plain LSTM)
     void *dh0;
     float *dc0;
-    float *dbpart;      // partial bias gradients: [8][4H] per XCD (XCD-local), [bgroups][4H] (generic)
+    float *dbpart;      // partial bias gradients: [8][4H] per XCD (XCD-local), [bgroups][4H] (generic),
+                        // [stepwise_db_rows(B)][4H] (stepwise plain layers)
     unsigned *sync;
 };
 hipError_t launch_backward(DType t, const RecShape &sh, const RecTiling &tl, const BwdBufs &b, hipStream_t s);

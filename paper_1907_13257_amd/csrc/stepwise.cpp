@@ -145,8 +145,8 @@ hipError_t backward_stepwise(DType t, const RecShape &sh, const BwdBufs &b, cons
         } else {
             const bool first = st == T - 1;
             const char *dy_t = static_cast<const char *>(b.dy) + (long)tt * B * sh.ldy * es;
-            RET_IF(gates_backward(t, B, H, nullptr, dy_t, sh.ldy, first ? nullptr : b.dhn, first ? b.dhT : nullptr,
-                                  gates_t, c_t, cprev, b.dcn, dz_t, dc0, K_REC_BWD, s));
+            RET_IF(gates_backward_db(t, B, H, dy_t, sh.ldy, first ? nullptr : b.dhn, first ? b.dhT : nullptr, gates_t,
+                                     c_t, cprev, b.dcn, dz_t, dc0, b.dbpart, first, K_REC_BWD, s));
         }
         if (st > 0 || b.dh0) {   // R^T dz_t: the recurrent gradient of the previous visited step
             GemmDesc g = base_desc(t, w);

@@ -413,3 +413,66 @@ def test_register_staged_products(dtype, tile, monkeypatch):
     monkeypatch.setenv("LSTM355_GEMM_TILE", tile)
     run_case(9, 61, 328, 264, 0, dtype, False, 328 ** -0.5)
     run_case(5, 33, 136, 72, 40, dtype, True, 136 ** -0.5)
+
+
+# Where plain layers leave the generic kernels for the stepwise sequence, and
+# just before: (T, B, H, dtype, reverse), (forward stepwise, backward stepwise)
+STEPWISE_RULE_CASES = [
+    ((2, 33, 3000, "bf16", False), (True, False)),    # three streamed tiles
+    ((2, 72, 3000, "bf16", True), (True, True)),      # five
+    ((2, 40, 2048, "f32", False), (False, False)),    # two
+    ((1, 40, 2048, "f32", True), (True, False)),      # one step, two streamed tiles
+    ((1, 3, 4096, "bf16", False), (False, False)),    # one step, one streamed tile
+    ((1, 33, 64, "f32", False), (True, False)),       # one step, the slice on chip
+    ((2, 512, 1024, "f32", False), (True, True)),     # sixteen tiles on chip; eight streamed backward
+    ((2, 6000, 16, "f32", True), (True, False)),      # a few cells, six tiles on chip
+]
+
+
+@pytest.mark.parametrize("case,stepwise", STEPWISE_RULE_CASES)
+def test_stepwise_rule(case, stepwise, monkeypatch):
+    T, B, H, dtype, reverse = case
+    gpu = run_case(T, B, 16, H, 0, dtype, reverse, H ** -0.5)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (gpu["tiling"][3] == 2000, gpu["tiling"][7] == 2000) == stepwise, gpu["tiling"]
+
+
+@pytest.mark.parametrize("T,B,H", [(6, 128, 2560), (2, 5, 1032)])
+def test_stepwise_bias_gradient_from_unrounded_sums(T, B, H, monkeypatch):
+    """A plain layer's db is the fp32 sum of dz before it is rounded to bf16 on
+    every path: the stepwise sequence's error is the generic kernels' within
+    the order of the sums.  A column sum of the rounded dz adds one rounding of
+    2^-9 per element, four to five times that error at these sizes."""
+    from paper_1907_13257_amd import Layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + B)
+
+    def uniform(*shape, dtype=torch.bfloat16):
+        return ((torch.rand(shape, generator=g, device="cuda") * 2 - 1) * H ** -0.5).to(dtype)
+
+    I = 32
+    W, R, b = uniform(4 * H, I), uniform(4 * H, H), uniform(4 * H, dtype=torch.float32)
+    x, dy = (torch.randn((T, B, n), generator=g, device="cuda").to(torch.bfloat16) for n in (I, H))
+    bd = b.double().requires_grad_(True)
+    h = torch.zeros(B, H, dtype=torch.double, device="cuda")
+    c, ys, Wd, Rd = h, [], W.double(), R.double()
+    for t in range(T):
+        i, f, u, o = (x[t].double() @ Wd.t() + h @ Rd.t() + bd).chunk(4, dim=1)
+        c = torch.sigmoid(f) * c + torch.sigmoid(i) * torch.tanh(u)
+        h = torch.sigmoid(o) * torch.tanh(c)
+        ys.append(h)
+    (torch.stack(ys) * dy.double()).sum().backward()
+    errs = {}
+    for recurrence in ("persistent", "stepwise"):
+        monkeypatch.setenv("LSTM355_RECURRENCE", recurrence)
+        lay = Layer(T, B, I, H, 0, "bf16")
+        y = torch.empty_like(dy)
+        grads = {"d" + k: torch.empty(v.shape, dtype=torch.float32, device="cuda")
+                 for k, v in dict(W=W, R=R, b=b).items()}
+        lay.forward(x, W, R, b, y=y)
+        lay.backward(dy, x, W, R, y, grads)
+        assert lay.check() == 0
+        errs[recurrence] = float((grads["db"].double() - bd.grad).norm() / bd.grad.norm())
+        lay.close()
+    announce(f"bias gradient T{T} B{B} H{H} " + ", ".join(f"{k}={v:.2e}" for k, v in errs.items()))
+    assert errs["stepwise"] <= 1.5 * errs["persistent"], errs
