@@ -248,7 +248,10 @@ __device__ __forceinline__ u32x4 pair_frag(const char *tilep, int c, int lane)
 // runs.  Per layer, T = 50, H = 1024: B = 512 forward 604 -> 440 us, backward
 // 733 -> 615 us; B = 264 (three blocks, the fourth not run) 480 -> 320 us and
 // 582 -> 400 us.  With two blocks the rows are not there in time (forward 237
-// -> 249 us at B = 256), so those copy at the start of their own block.  What
+// -> 249 us at B = 256), so those copy at the start of their own block; so does
+// the forward of 256 and 512 cells, whose blocks are too short (B = 512, T = 50,
+// I = 256, with the input projection: 297 us in flight, 261 not, and 399 / 360),
+// while their backward gains (569 -> 472 us and 766 -> 604).  What
 // bounds a block now: forward, in cycles of about 4900, the matrix cores 1024
 // of 1450-1950 spent on the product, 512 each writing and reading the partial
 // sums, and the barriers' skew; backward the copy, 128 KiB at the CU's 64
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
     const bool has_cell = tid < NCELL && (!PAD || cj < H);
     __shared__ int s_bad;
 
-    if constexpr (MBX > 2) {
+    if constexpr (MBX > 2 && HN >= 32) {
         if (tid == 0) s_bad = 0;   // ordered by the first barrier below
         // Pipelined row blocks: see PipeRows.  The input projection of a block
         // is loaded one block ahead, before the copy of that block's rows.
@@ -935,10 +938,12 @@ __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
             // values nobody stores) and only the stores depend on the lane:
             // the input projection loaded for this step is then consumed on
             // every path, and the next step's loads do not wait for these
-            // loads, nor for the stores issued after them.
+            // loads, nor for the stores issued after them.  With four row
+            // blocks the registers run short and the lanes without a row skip it.
+            constexpr bool ALL_LANES = MBX <= 2;
             const int b = rb0 + cr;
             const int crr = has_cell ? cr : 0;
-            {
+            if (ALL_LANES || (has_cell && b < rowend)) {
                 float z[4];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
