@@ -789,7 +789,7 @@ extern "C" lstm_status_t lstm_backward(lstm_handle_t h, const void *dy, const vo
                 g.side.sum_dst = db;
                 g.side.sum_acc = accumulate;
             }
-            if (gemm_dual_ok(g) && gemm_dual_pays(g)) {
+            if (gemm_dual_ok(g) && gemm_dual_pays(g, split_ws, h->split_floats)) {
                 TRY_HIP("dW|dR", gemm(g, s, K_GEMM_DWR));
                 fused = true;
             }

@@ -1601,13 +1601,33 @@ bool gemm_dual_ok(const GemmDesc &d)
     return dl_ok(d);
 }
 
-// One product saves the other's launch, its reads of A and both split-K
-// reductions, but is not split: with fewer 128x128 tiles than CUs each tile's
-// whole K is one workgroup's work.  Measured, one product against two split:
-// H = I = 256 K = 1600 22 / 32 us, 6400 67 / 58, 25600 251 / 173; H = I = 512
-// (128 tiles) K = 1600 24 / 45, 6400 71 / 70, 25600 311 / 195; H = I = 1024
-// (512 tiles) K = 6400 110 / 153.
-bool gemm_dual_pays(const GemmDesc &d) { return dual_tiles(d, 128) >= 256 || d.K <= 4096; }
+// Whether [dW | dR] should run as one product rather than as two split along
+// K.  One saves a launch, the reductions, the separate sum of db and, where the
+// first step's h0 is one of its segments, a third product, but each tile's whole
+// K is one workgroup's work.  In microseconds: a 128x128 tile takes 9.5 ns per k,
+// growing with the workgroups that share the chip (H = I = 256, 32 tiles, K =
+// 25600 251; H = I = 512, 128 tiles, 311; H = I = 1024, 512 tiles, K = 6400
+// 110); partials move at 5 TB/s.  One / two: H = I = 256 K = 1600 22 / 32, 6400
+// 67 / 58, 25600 251 / 173, with h0 5632 62 / 73; H = I = 512 1600 24 / 45, 6400
+// 71 / 70, 25600 311 / 195; backward passes with I = 1024, H = 512, K = 4608 155
+// / 167, with h0 and I = 64, H = 256, K = 8192 190 / 169.
+bool gemm_dual_pays(const GemmDesc &d, float *splitk_ws, size_t splitk_ws_floats)
+{
+    const long tiles = dual_tiles(d, 128);
+    if (tiles >= 256) return true;
+    auto tiled = [](double items, double k) { return k * (0.0095 + 1.37e-5 * items); };
+    auto alone = [&](int n) {
+        GemmDesc g{};
+        g.in = d.in; g.out_f32 = true; g.a_kmajor = false; g.b_kmajor = false;
+        g.M = d.M; g.N = n; g.K = d.K; g.lda = d.lda; g.ldb = d.ldb; g.beta = d.beta;
+        g.splitk_ws = splitk_ws; g.splitk_ws_floats = splitk_ws_floats;
+        const int sp = fit_splits(g, choose(g, 2).splits);
+        const double t = (double)((d.M + 127) / 128) * ((n + 127) / 128);
+        return tiled(t * sp, (double)d.K / sp) + (sp > 1 ? 5.0 + (sp + 1.0) * d.M * n * 4.0 / 5.0e6 : 0.0);
+    };
+    const double two = alone(d.N1) + alone(d.N - d.N1) + 7.0 + (d.B3 ? 12.0 + 0.01 * d.hlen : 0.0);
+    return tiled((double)tiles, d.K) <= two;
+}
 
 // fp16 C only where the product takes the 256x256 tile unsplit (the same
 // shapes on which choose() picks it: more than 1024 rows, at least 192 tiles).

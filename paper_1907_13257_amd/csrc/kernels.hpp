@@ -119,8 +119,9 @@ bool gemm_f16_ok(const GemmDesc &d);
 hipError_t gemm(const GemmDesc &d, hipStream_t s, int kclass);
 // Whether a descriptor with a second column block (N1 > 0) can run.
 bool gemm_dual_ok(const GemmDesc &d);
-// Whether it should run as one product rather than as two split along K.
-bool gemm_dual_pays(const GemmDesc &d);
+// Whether it should run as one product rather than as two split along K (with
+// these floats of workspace for their partials).
+bool gemm_dual_pays(const GemmDesc &d, float *splitk_ws, size_t splitk_ws_floats);
 
 // Small kernels.
 // dst[c][r] = src[r][c]; `side` (optional) is done by the same launch.
