@@ -479,8 +479,7 @@ void gemm_dl_kernel(GemmArgs g)
     // turn, so each XCD takes a contiguous share of the tiles (and every split
     // of them) or, split_major, of the splits (and every tile of them): few
     // tiles split many ways then read each k range of both operands on one XCD.
-    // (Only in the configuration that the long-K skinny products take, so that
-    // the smallest products do not pay for the test.)
+    // (Only in the configuration that the long-K skinny products take.)
     constexpr bool SPLIT_MAJOR = BM == 128 && BN == 128 && KD == 64 && NS == 4;
     int tile, split_id = blockIdx.y;
     bool idle;
@@ -1053,11 +1052,11 @@ hipError_t launch_gemm_dl(const GemmDesc &d, int splits, hipStream_t s)
     g.kchunk = ((d.K + splits - 1) / splits + KD - 1) / KD * KD;
     splits = (d.K + g.kchunk - 1) / g.kchunk;
     if (d.partials > 1 && splits != d.partials) return hipErrorInvalidValue;
-    // from eight splits on an XCD has whole splits to itself.  The LSTMP carry
+    // from 16 splits on an XCD has whole splits to itself.  The LSTMP carry
     // 128 x 1024 x 32768 split 32 ways 25 -> 20 us, BigLSTM's step 2560 -> 2454
     // us; at H = 4096, Hp = 512, 64 rows 1356 -> 1228 us; from two splits on
-    // BigLSTM took 2486 us
-    g.split_major = splits >= 8;
+    // BigLSTM took 2486 us, and with eight 64 x 2048 x 2048 went from 8.0 to 8.5 us
+    g.split_major = splits >= 16;
     g.partial = splits > 1 ? d.splitk_ws : nullptr;
     g.N1 = d.N1;
     g.B2 = static_cast<const char *>(d.B2); g.ldb2 = d.ldb2;
