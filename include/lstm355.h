@@ -223,8 +223,9 @@ size_t lstm_backward_stack_workspace_size(int L, const lstm_handle_t *h);
  * launch but relies on the device not running other kernels beside them;
  * if it does, their waits time out and lstm_check reports LSTM_ERR_TIMEOUT.
  * Use the cooperative launch when other streams (for example collectives
- * overlapping the backward pass) share the device.  Widths other than 256,
- * 512 and 1024, fp32 and LSTMP layers always launch cooperatively. */
+ * overlapping the backward pass) share the device.  The persistent kernels of
+ * other widths and of fp32 and LSTMP layers always launch cooperatively; the
+ * stepwise sequences have no kernel that waits for another workgroup. */
 
 /* Synchronises `stream` and reports whether any kernel of the library gave up
  * waiting on the current device since the last check
@@ -246,8 +247,10 @@ const char *lstm_last_error_detail(void);
 /* Diagnostics: the tiling chosen for this handle on the current device.
  * out8 = {fwd workgroups, fwd cells per workgroup, fwd batch rows per tile,
  * fwd variant, bwd workgroups, bwd cells per workgroup, bwd batch rows per
- * tile, bwd variant}; a workgroup count of 0 means no tiling fits.  Variant
- * 1000 marks the XCD-local kernels (bf16, plain LSTM, H in {256, 512, 1024}:
+ * tile, bwd variant}.  Variant 2000 (no workgroups) marks the stepwise
+ * sequence of products and cell updates: layers without a persistent tiling,
+ * wide LSTMP layers, and directions of plain layers that it runs faster.
+ * Variant 1000 marks the XCD-local kernels (bf16, plain LSTM, H in {256, 512, 1024}:
  * each XCD owns ceil(B/8) batch rows, each workgroup H/32 cells), 1001 the
  * same kernels on any other H up to 1024 (8, 16 or 32 cells per workgroup). */
 lstm_status_t lstm_describe_tiling(lstm_handle_t h, int *out8);

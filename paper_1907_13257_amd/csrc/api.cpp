@@ -878,7 +878,7 @@ extern "C" lstm_status_t lstm_check(lstm_handle_t h, void *workspace, void *stre
         return LSTM_ERR_UNSUPPORTED;
     }
     if (tripped) {
-        std::snprintf(g_detail, sizeof(g_detail), "a grid barrier's watchdog expired");
+        std::snprintf(g_detail, sizeof(g_detail), "a kernel's wait expired (watchdog)");
         return LSTM_ERR_TIMEOUT;
     }
     return LSTM_OK;

@@ -330,7 +330,7 @@ hipError_t forward_stepwise(DType t, const RecShape &sh, const FwdBufs &b, const
 hipError_t backward_stepwise(DType t, const RecShape &sh, const BwdBufs &b, const StepwiseArgs &w, hipStream_t s);
 
 // Reads (synchronously) and clears the library's sticky watchdog word on the
-// current device: nonzero if a grid barrier gave up since the last call.
+// current device: nonzero if a kernel's wait gave up since the last call.
 hipError_t watchdog_read_and_clear(unsigned *tripped);
 
 }  // namespace lstm355

@@ -1,6 +1,6 @@
 // pointwise.hip -- bandwidth-bound helpers of the LSTM step: weight
 // transposes for the backward pass, the bias gradient (column sums of dz),
-// stack composition adds, and word fills for barrier counters.
+// stack composition adds, the stepwise recurrences' cell updates, and word fills.
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "side_job.hpp"

@@ -1,6 +1,7 @@
 // recurrent.hip -- the sequential part of the LSTM step for the layers that do
 // not fit the XCD-local kernels (fp32 storage, LSTMP, bf16 cells wider than
-// 1024): one persistent, cooperatively launched kernel for the forward
+// 1024 or more than 512 rows) and have a tiling here (up to 4096 cells): one
+// persistent, cooperatively launched kernel for the forward
 // recurrence and one for back-propagation through time.
 //
 // Ownership.  Workgroup (ht, bg) owns the cells j in [ht*HN, ht*HN + HN) for
@@ -28,7 +29,8 @@
 //
 // Products.  The eight waves split k; a wave reads the exchanged rows straight
 // into MFMA operand registers (each element once per workgroup), eight 64-byte
-// chunks of k in flight while the previous eight are multiplied, so a product
+// chunks of k in flight while the previous eight are multiplied (four with 64
+// rows per tile; four or two where the weights stream as well), so a product
 // is bound by the rows' bytes and not by one memory latency per chunk (f32,
 // H = 1024, K = 4096: one chunk in flight took 64 us per step).  The eight
 // partial sums meet in LDS.

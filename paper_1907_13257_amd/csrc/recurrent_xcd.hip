@@ -245,9 +245,9 @@ __device__ __forceinline__ u32x4 pair_frag(const char *tilep, int c, int lane)
 // while the block before is still worked on: forward, as soon as its fragments
 // are read (the wave's LDS tile is then free), backward, pair by pair during
 // its product; they land while its partial sums are reduced and its gate math
-// runs.  Per layer, T = 50, H = 1024: B = 512 forward 604 -> 440 us, backward
-// 733 -> 615 us; B = 264 (three blocks, the fourth not run) 480 -> 320 us and
-// 582 -> 400 us.  With two blocks the rows are not there in time (forward 237
+// runs.  Average launch, T = 50, H = 1024, both in turn on one box: B = 512
+// forward 619 -> 463 us, backward 710 -> 605; B = 264 (three blocks, the fourth
+// not run) 474 -> 324 and 574 -> 418.  With two blocks the rows are not there in time (forward 237
 // -> 249 us at B = 256), so those copy at the start of their own block; so does
 // the forward of 256 and 512 cells, whose blocks are too short (B = 512, T = 50,
 // I = 256, with the input projection: 297 us in flight, 261 not, and 399 / 360),
@@ -284,7 +284,8 @@ struct PipeRows {
 // p ^ pperm of the slice (and the caller's weights are loaded in that order).
 // The workgroups of an XCD copy the same rows at the same time; taking their
 // pairs in different orders (pperm from the slot) they ask the L2 for different
-// lines (B = 512 backward 662 -> 611 us per layer, B = 256 305 -> 297 us).
+// lines (B = 512 backward 662 -> 611 us per layer; with two blocks, B = 256, the
+// launch measured 305 -> 297 us on one box and 300 / 302 on another).
 template <int KCW, bool PAD>
 struct PipePairs {
     u32x4 rs;
@@ -695,8 +696,9 @@ struct XFwdArgs {
 // leaves at once, the resident rows and columns at or past H are zero
 // registers, and the copies read zero past a row's H elements (neighbouring
 // rows may still hold NOT_READY, a NaN).  A step costs what the full width
-// costs, set by the exchange: H = 648 at 50 rows 26.4 -> 2.1 us per forward
-// step against the generic kernel, whose grid-wide barrier alone takes 24.5 us.
+// costs, set by the exchange: H = 648 at 50 rows 2.0 us per forward step (the
+// generic kernel with its former grid-wide barrier 26.4; xcd_path_ok has the
+// comparison with the generic kernels as they are).
 template <int HN, int MBX, bool GX16 = false, bool ACT16 = false, bool PAD = false>
 __global__ __launch_bounds__(XT) void lstm_fwd_xcd(XFwdArgs a)
 {
@@ -1533,8 +1535,8 @@ __device__ __forceinline__ void act_f32(const unsigned (&bits)[4], float (&v)[4]
 // Wave w multiplies the k range [w*H/2, (w+1)*H/2) of dh_{t-1} = R^T dz_t
 // (k over the 4H gate rows); the eight partial sums meet in LDS.
 // PAD: H is any multiple of 8 up to 32*HN, as in the forward; k runs over the
-// 4H gate rows as they lie in dz, zero past them (H = 648 at 50 rows 31.5 ->
-// 2.6 us per step against the generic kernel).
+// 4H gate rows as they lie in dz, zero past them (H = 648 at 50 rows 2.5 us per
+// step).
 template <int HN, int MBX, bool ACT16 = false, bool PAD = false>
 __global__ __launch_bounds__(XT) void lstm_bwd_xcd(XBwdArgs a)
 {

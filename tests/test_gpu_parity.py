@@ -334,8 +334,8 @@ def test_watchdog_gives_up_from_host_and_next_call_succeeds(T, B, I, H, dtype, m
     persistent recurrence's waits give up instead of waiting: every wave
     exits (the launch completes), lstm_check reports LSTM_ERR_TIMEOUT, and
     the next calls with the normal watchdog give the oracle's results.  The
-    generic kernel's grid barrier always trips (the first workgroup to arrive
-    finds the others missing); the XCD-local kernel trips when any wave's
+    generic kernel's wait for its group's step flags always trips (the first
+    workgroup to arrive finds the others missing); the XCD-local kernel trips when any wave's
     first copy of the exchanged rows is incomplete, which is not certain."""
     from paper_1907_13257_amd import Layer, lstm355
     label = f"watchdog T{T} B{B} I{I} H{H} {dtype}"
