@@ -94,9 +94,17 @@ __device__ __forceinline__ int stage_swz(int r)
 // different lines of L2 (measured: 2% faster for the forward's four
 // instructions per wave, slower for the backward's sixteen).  PAD: bytes of a
 // row at or past kend read as zero (an offset past the descriptor's end).
+// LANE: the lane's range is stated here.  This is optimised before it is
+// inlined, and other callers hide the range: without it the forward wavefront of
+// one row block spills 44 instead of 16 bytes where layers are residual and took
+// 9 % longer (T = 20, 8 rows, three layers 90 / 98 us), and without residual
+// layers 1 to 2 % (T = 10, 16 rows, three layers 59.2 / 60.6).  Stated
+// everywhere, it made the backward wavefront 13 % slower (GNMT-4 at 16 rows 214 /
+// 243 us) and the residual forward of two row blocks 5 to 7 % (48 bytes of
+// spills instead of 20).
 constexpr unsigned OOB_OFFSET = 0x80000000u;
 
-template <int RB, bool COHERENT = false, bool ROT = false, bool PAD = false>
+template <int RB, bool COHERENT = false, bool ROT = false, bool PAD = false, bool LANE = false>
 __device__ __forceinline__ void stage_rows(u32x4 rs, long r0, long ld, int kbyte, unsigned tile, int lane,
                                            unsigned qmask = ~0u, int rot = 0, int kend = 0)
 {
@@ -107,7 +115,7 @@ __device__ __forceinline__ void stage_rows(u32x4 rs, long r0, long ld, int kbyte
     for (int qi = 0; qi < NQ; ++qi) {
         const int q = ROT ? (qi + rot) & (NQ - 1) : qi;
         if (!((qmask >> q) & 1u)) continue;   // wave-uniform
-        const int o = q * 1024 + lane * 16;
+        const int o = q * 1024 + (LANE ? lane & 63 : lane) * 16;
         const int r = o / RB, p = (o % RB) >> 4;
         const int c = p ^ stage_swz<RB>(r);
         unsigned voff = (unsigned)((r0 + r) * ld * 2 + kbyte + c * 16);
@@ -160,7 +168,7 @@ __device__ __forceinline__ bool saw_not_ready(u16x2 m) { return m.x == NOT_READY
 // and multiplies it while checking for NOT_READY; an attempt that saw one is
 // discarded and repeated.  Returns false if another workgroup aborted or the
 // wall-clock watchdog expired (then the abort word is raised).
-template <int RB, int KCW, int NBX, bool WT = false, bool PAD = false>
+template <int RB, int KCW, int NBX, bool WT = false, bool PAD = false, bool LANE = false>
 __device__ __forceinline__ bool stage_mma_when_ready(u32x4 rs, long r0, long ld, int kbyte, unsigned tile,
                                                      const char *tilep, int lane, int valid,
                                                      const u32x4 (&rf)[NBX][KCW], f32x4 (&acc)[NBX],
@@ -179,7 +187,7 @@ __device__ __forceinline__ bool stage_mma_when_ready(u32x4 rs, long r0, long ld,
     for (int q = 0; q < 16 / RPI; ++q)
         if (q * RPI < valid) qmask |= 1u << q;
     while (true) {
-        stage_rows<RB, true, WT, PAD>(rs, r0, ld, kbyte, tile, lane, qmask, rot, kend);
+        stage_rows<RB, true, WT, PAD, LANE>(rs, r0, ld, kbyte, tile, lane, qmask, rot, kend);
         const unsigned ab = __builtin_amdgcn_raw_buffer_load_b32(rfl, XCD_ABORT * 4, 0, 16);
         wait_own_loads();
 #pragma unroll
@@ -603,7 +611,7 @@ __device__ __forceinline__ u32x4 bf16_add8(u32x4 a, u32x4 b)
 // Once every element is final and `store` is set, the wave also stores its
 // slice of the summed rows into `rsum` with device-coherent stores (one
 // workgroup per XCD stores them; each element is written once).
-template <int RB, int KCW, int NBX>
+template <int RB, int KCW, int NBX, bool LANE>
 __device__ __forceinline__ bool stage_sum_mma_when_ready(u32x4 rsa, u32x4 rsb, bool poll_a, bool poll_b, long r0,
                                                          long ld, int kbyte, unsigned tile_a, const char *tpa,
                                                          unsigned tile_b, const char *tpb, int lane, int valid,
@@ -622,13 +630,13 @@ __device__ __forceinline__ bool stage_sum_mma_when_ready(u32x4 rsa, u32x4 rsb, b
         if (q * RPI < valid) qmask |= 1u << q;
     while (true) {
         if (poll_a)
-            stage_rows<RB, true>(rsa, r0, ld, kbyte, tile_a, lane, qmask);
+            stage_rows<RB, true, false, false, LANE>(rsa, r0, ld, kbyte, tile_a, lane, qmask);
         else
-            stage_rows<RB, false>(rsa, r0, ld, kbyte, tile_a, lane, qmask);
+            stage_rows<RB, false, false, false, LANE>(rsa, r0, ld, kbyte, tile_a, lane, qmask);
         if (poll_b)
-            stage_rows<RB, true>(rsb, r0, ld, kbyte, tile_b, lane, qmask);
+            stage_rows<RB, true, false, false, LANE>(rsb, r0, ld, kbyte, tile_b, lane, qmask);
         else
-            stage_rows<RB, false>(rsb, r0, ld, kbyte, tile_b, lane, qmask);
+            stage_rows<RB, false, false, false, LANE>(rsb, r0, ld, kbyte, tile_b, lane, qmask);
         const unsigned ab = __builtin_amdgcn_raw_buffer_load_b32(rfl, XCD_ABORT * 4, 0, 16);
         wait_own_loads();
 #pragma unroll
@@ -1046,6 +1054,7 @@ __device__ __forceinline__ unsigned ready_f32(float v)
 template <int HN, int MBX, bool RES = false>
 __global__ __launch_bounds__(XT) void lstm_fwd_wave(XWaveArgs a)
 {
+    constexpr bool LANE = !(RES && MBX == 2);   // see stage_rows
     constexpr int NT = 4 * HN;        // gate rows owned (i, f, g, o of HN cells)
     constexpr int NB = NT / 16;
     constexpr int KW = 4 * HN;        // k per wave (H / 8)
@@ -1107,7 +1116,7 @@ __global__ __launch_bounds__(XT) void lstm_fwd_wave(XWaveArgs a)
                 for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
                 if (from_x) {
                     if (s > 0 || mb > 0) wait_own_lds();   // the previous block's fragment reads are done
-                    stage_rows<RB>(rs_x, (long)s * B + rb0, H, w * KW * 2, tile, lane);
+                    stage_rows<RB, false, false, false, LANE>(rs_x, (long)s * B + rb0, H, w * KW * 2, tile, lane);
                     wait_own_loads();
 #pragma unroll
                     for (int c = 0; c < KCW; ++c) {
@@ -1120,17 +1129,17 @@ __global__ __launch_bounds__(XT) void lstm_fwd_wave(XWaveArgs a)
                     const u32x4 rs_b = buffer_desc(ly.in_b, (long)a.T * B * H * 2);
                     const __amdgpu_buffer_rsrc_t rsum =
                         __builtin_amdgcn_make_buffer_rsrc(ly.sum, (short)0, (int)((long)a.T * B * H * 2), 0x00020000);
-                    if (!stage_sum_mma_when_ready<RB, KCW, NB>(rs_x, rs_b, true, ly.poll_b != 0, (long)s * B + rb0, H,
-                                                               w * KW * 2, tile, stage[w],
-                                                               lds_addr(&stage_b[RES ? w : 0][0]),
-                                                               stage_b[RES ? w : 0], lane, B - rb0, rf, acc, rsum,
-                                                               slot == 0, a.flags, a.timeout))
+                    if (!stage_sum_mma_when_ready<RB, KCW, NB, LANE>(rs_x, rs_b, true, ly.poll_b != 0,
+                                                                     (long)s * B + rb0, H, w * KW * 2, tile, stage[w],
+                                                                     lds_addr(&stage_b[RES ? w : 0][0]),
+                                                                     stage_b[RES ? w : 0], lane, B - rb0, rf, acc,
+                                                                     rsum, slot == 0, a.flags, a.timeout))
                         s_bad = 1;
                 } else {
                     if (mb > 0) wait_own_lds();
-                    if (!stage_mma_when_ready<RB, KCW, NB, true>(rs_x, (long)s * B + rb0, H, w * KW * 2, tile,
-                                                                 stage[w], lane, B - rb0, rf, acc, a.flags, a.timeout,
-                                                                 slot))
+                    if (!stage_mma_when_ready<RB, KCW, NB, true, false, LANE>(
+                            rs_x, (long)s * B + rb0, H, w * KW * 2, tile, stage[w], lane, B - rb0, rf, acc, a.flags,
+                            a.timeout, slot))
                         s_bad = 1;
                 }
 #pragma unroll
@@ -1186,9 +1195,9 @@ __global__ __launch_bounds__(XT) void lstm_fwd_wave(XWaveArgs a)
             for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (mb > 0) wait_own_lds();   // the previous block's fragment reads are done
             if (s > 0) {
-                if (!stage_mma_when_ready<RB, KCW, NB, true>(rs_y, (long)(s - 1) * B + rb0, H, w * KW * 2, tile,
-                                                             stage[w], lane, B - rb0, rf, acc, a.flags, a.timeout,
-                                                             slot))
+                if (!stage_mma_when_ready<RB, KCW, NB, true, false, LANE>(
+                        rs_y, (long)(s - 1) * B + rb0, H, w * KW * 2, tile, stage[w], lane, B - rb0, rf, acc, a.flags,
+                        a.timeout, slot))
                     s_bad = 1;
             }
 #pragma unroll
